@@ -11,7 +11,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libscocg.so")
-SOURCES = ["kernels.hip", "flush.hip", "krylov.hip", "api.hip"]
+SOURCES = ["kernels.hip", "seed_block.hip", "flush.hip", "krylov.hip", "api.hip"]
 HEADERS = ["scocg_internal.h", "device_common.h", "krylov.h", "hubbard_rows.h"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -661,6 +661,8 @@ int solve(SolveRequest &rq, hipStream_t st)
     s.spmv_rb = pairable ? 2 : 1;
     for (int64_t j = 0; j < K; ++j) (hdesc[j].hub ? s.has_hub : s.has_sell) = 1;
     for (int64_t j = 0; j < K; ++j) (hdesc[j].n >= RED_BIG_ROWS ? s.has_red_big : s.has_red_small) = 1;
+    for (int64_t j = 0; j < K; ++j) s.max_w = std::max(s.max_w, (rq.Hj.empty() ? rq.H : rq.Hj[j])->d.max_w);
+    s.seed_block = !s.has_hub && seed_block_fits(n, K);
     s.hub_lds = 1;
     for (int64_t j = 0; j < K; ++j) {
         const DevCSR &dj = (rq.Hj.empty() ? rq.H : rq.Hj[j])->d;
@@ -859,7 +861,7 @@ int solve(SolveRequest &rq, hipStream_t st)
     HIPCHK(launch_init(s, rq.B, rq.unit_idx ? bidx.as<int64_t>() : nullptr, bsd.as<int32_t>(), limit, st));
 
     PinnedBuf host_state;
-    HIPCHK(host_state.alloc(K * sizeof(SeedState)));
+    HIPCHK(host_state.alloc(2 * K * sizeof(SeedState)));
     SeedState *hs = (SeedState *)host_state.ptr;
 
     std::vector<hipEvent_t> evs;
@@ -901,7 +903,7 @@ int solve(SolveRequest &rq, hipStream_t st)
     }
     const hipStream_t sf = fs.sf;
     hipEvent_t evPS[2], evFL[2];
-    for (int q = 0; q < 2; ++q) {
+    for (int q = 0; overlap && q < 2; ++q) {
         HIPCHK(new_event(evPS[q], hipEventDisableTiming));
         HIPCHK(new_event(evFL[q], hipEventDisableTiming));
     }
@@ -936,13 +938,15 @@ int solve(SolveRequest &rq, hipStream_t st)
     // A, one per parity) on `st`; the deferred update on the update stream; the captured
     // end-of-block decisions (graph B) on `st`.  Graphs are captured on a private stream.
     GraphPair gr;
-    const bool use_graph = !o.no_graph;
+    // With the block's iterations in one launch (seed_block) a block is five launches, which the
+    // host issues faster than the GPU runs them: no graph is captured.
+    const bool use_graph = !o.no_graph && !s.seed_block;
     if (use_graph) {
         HIPCHK(hipStreamCreateWithFlags(&gr.cap, hipStreamNonBlocking));
         for (int q = 0; q < 2; ++q) {
             HIPCHK(hipStreamBeginCapture(gr.cap, hipStreamCaptureModeThreadLocal));
             HIPCHK(launch_switch_vectors(sp[q], gr.cap));
-            for (int t = 0; t < TB; ++t) HIPCHK(launch_seed_iteration(sp[q], gr.cap));
+            HIPCHK(launch_block_iterations(sp[q], gr.cap));
             HIPCHK(launch_pair_scalars(sp[q], gr.cap));
             HIPCHK(hipStreamEndCapture(gr.cap, &gr.ga[q]));
             HIPCHK(hipGraphInstantiate(&gr.ea[q], gr.ga[q], nullptr, nullptr, 0));
@@ -960,19 +964,28 @@ int solve(SolveRequest &rq, hipStream_t st)
     const int64_t max_blocks = (int64_t)K * ((int64_t)limit + 4 * M + 8) + 8 + per_sync;
     int64_t blocks = 0;
     bool done = false;
+    // A block of five launches is too short to wait for the host's look at the states after each:
+    // the next round is launched first (a round too many costs its empty launches, about 15 us).
+    const bool ahead = s.seed_block != 0;
+    int64_t rounds = 0;
+    hipEvent_t evST[2] = {};
+    if (ahead)
+        for (int q = 0; q < 2; ++q) HIPCHK(new_event(evST[q], hipEventDisableTiming));
     while (!done) {
         for (int b = 0; b < per_sync; ++b) {
             const int par = (int)(blocks & 1);
-            if (blocks >= 2) HIPCHK(hipStreamWaitEvent(st, evFL[par], 0));
+            if (overlap && blocks >= 2) HIPCHK(hipStreamWaitEvent(st, evFL[par], 0));
             if (use_graph) {
                 HIPCHK(hipGraphLaunch(gr.ea[par], st));
             } else {
                 HIPCHK(launch_switch_vectors(sp[par], st));
-                for (int t = 0; t < TB; ++t) HIPCHK(launch_seed_iteration(sp[par], st));
+                HIPCHK(launch_block_iterations(sp[par], st));
                 HIPCHK(launch_pair_scalars(sp[par], st));
             }
-            HIPCHK(hipEventRecord(evPS[par], st));
-            HIPCHK(hipStreamWaitEvent(sf, evPS[par], 0));
+            if (overlap) {
+                HIPCHK(hipEventRecord(evPS[par], st));
+                HIPCHK(hipStreamWaitEvent(sf, evPS[par], 0));
+            }
             const int slot = (int)(blocks % NE);
             if (g_profiling) {
                 HIPCHK(collect(slot));
@@ -983,17 +996,31 @@ int solve(SolveRequest &rq, hipStream_t st)
                 HIPCHK(hipEventRecord(fev[2 * slot + 1], sf));
                 fev_pending[slot] = true;
             }
-            HIPCHK(hipEventRecord(evFL[par], sf));
+            if (overlap) HIPCHK(hipEventRecord(evFL[par], sf));
             if (use_graph) HIPCHK(hipGraphLaunch(gr.eb, st));
             else HIPCHK(launch_block_finalize(sp[par], st));
             ++blocks;
         }
-        HIPCHK(hipMemcpyAsync(hs, s.seed, K * sizeof(SeedState), hipMemcpyDeviceToHost, st));
-        HIPCHK(hipStreamSynchronize(st));
+        SeedState *now = hs + (ahead ? rounds % 2 : 0) * K;
+        HIPCHK(hipMemcpyAsync(now, s.seed, K * sizeof(SeedState), hipMemcpyDeviceToHost, st));
+        if (ahead) {
+            // look at the round before, while this one runs
+            HIPCHK(hipEventRecord(evST[rounds % 2], st));
+            if (++rounds == 1) continue;
+            HIPCHK(hipEventSynchronize(evST[rounds % 2]));
+            now = hs + (rounds % 2) * K;
+        } else {
+            HIPCHK(hipStreamSynchronize(st));
+        }
         done = true;
         for (int64_t j = 0; j < K; ++j)
-            if (hs[j].status != SEED_STOPPED) done = false;
+            if (now[j].status != SEED_STOPPED) done = false;
         if (blocks > max_blocks) return fail(SCOCG_EHIP, "iteration driver did not terminate");
+    }
+    if (ahead) {
+        // the last round found every rhs stopped and changed nothing
+        HIPCHK(hipStreamSynchronize(st));
+        blocks -= per_sync;
     }
     HIPCHK(hipStreamSynchronize(sf));
     if (g_profiling)
@@ -1777,6 +1804,8 @@ extern "C" int greens_diag_noalloc(scocg_csr_t H, int64_t n_shift, const double 
     s.spmv_rb = K >= 2 ? 2 : 1;
     (d.d_hub ? s.has_hub : s.has_sell) = 1;
     (n >= RED_BIG_ROWS ? s.has_red_big : s.has_red_small) = 1;
+    s.max_w = d.max_w;
+    s.seed_block = !s.has_hub && seed_block_fits(n, K);
     s.hub_lds = 1;
     if (d.d_hub) {
         if (d.hub_Dd > HUB_LDS_MAX || n / d.hub_Dd > (n + 255) / 256) s.hub_lds = 0;
@@ -1842,14 +1871,16 @@ extern "C" int greens_diag_noalloc(scocg_csr_t H, int64_t n_shift, const double 
         sp[q].nact = L.nact + q * KM;
         sp[q].blk = L.blk + q * (size_t)K * 4;
     }
-    const int per_sync = std::max(1, 64 / TB);
+    // (with the block's iterations in one launch the look, about 30 us, is a sixth of a block: taken
+    // every fourth one, blocks past the last cost their empty launches)
+    const int per_sync = s.seed_block ? std::max(4, 64 / TB) : std::max(1, 64 / TB);
     const int64_t max_blocks = (int64_t)K * ((int64_t)limit + 4 * M + 8) + 8 + per_sync;
     int64_t blocks = 0;
     for (;;) {
         for (int b = 0; b < per_sync; ++b) {
             const int par = (int)(blocks & 1);
             HIPCHK(launch_switch_vectors(sp[par], st));
-            for (int t = 0; t < TB; ++t) HIPCHK(launch_seed_iteration(sp[par], st));
+            HIPCHK(launch_block_iterations(sp[par], st));
             HIPCHK(launch_pair_scalars(sp[par], st));
             HIPCHK(launch_flush(sp[par], st));
             HIPCHK(launch_block_finalize(sp[par], st));

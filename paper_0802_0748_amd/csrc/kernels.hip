@@ -258,25 +258,6 @@ __device__ inline void reset_counter(uint32_t *cnt, int64_t j)
     if (threadIdx.x == 0) __hip_atomic_store(&cnt[j], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__device__ inline bool seed_running(const SeedState &st, int TB)
-{
-    return st.status == SEED_RUNNING && st.step < TB;
-}
-
-__device__ inline double2 *ring_slot(const SolveDev &s, int slot, const RhsDesc &d)
-{
-    return s.ring + (int64_t)slot * s.ntot + d.voff;
-}
-
-// Seed directions.  With two right-hand sides per SpMV thread (rhs 2i and 2i+1 share one
-// matrix, so voff_{2i+1} = voff_{2i} + n) the pair is interleaved element by element from
-// voff_{2i} on: one gather of 32 bytes serves both.  Otherwise p_j is the plain vector at voff_j.
-__device__ inline int64_t p_index(const SolveDev &s, int64_t j, const RhsDesc &d, int64_t row)
-{
-    if (s.spmv_rb == 2) return d.voff - (j & 1) * d.n + 2 * row + (j & 1);
-    return d.voff + row;
-}
-
 // ---------------------------------------------------------------------------------------
 // initialisation: r_0 = b, p = 0, rho = b.b, ||b||, seed state
 // ---------------------------------------------------------------------------------------
@@ -452,15 +433,6 @@ __device__ inline bool xcd_group_block(int64_t nblk, int64_t G, int64_t &g, int6
     rb = t % nblk;
     return g < G;
 }
-
-// Matrix arrays reached through a descriptor are global memory; saying so lets the compiler
-// use global (not flat) loads, which wait on the vector-memory counter only.
-template <typename T>
-__device__ inline const __attribute__((address_space(1))) T *gptr(const T *p)
-{
-    return (const __attribute__((address_space(1))) T *)p;
-}
-
 
 // Row `row` of H p for the matrix-free Hubbard operator, for RB right-hand sides whose p at
 // row c is pv[RB * c + b].  The terms are added in the column order of the stored matrix
@@ -1642,6 +1614,16 @@ hipError_t launch_seed_iteration(const SolveDev &s, hipStream_t st)
     if (s.has_red_small) hipLaunchKernelGGL(k_beta<WG>, dim3((unsigned)s.K), dim3(WG), 0, st, s);
     if (s.has_red_big) hipLaunchKernelGGL(k_beta<RWG_BIG>, dim3((unsigned)s.K), dim3(RWG_BIG), 0, st, s);
     return hipGetLastError();
+}
+
+hipError_t launch_block_iterations(const SolveDev &s, hipStream_t st)
+{
+    if (s.seed_block) return launch_seed_block(s, st);
+    for (int t = 0; t < s.TB; ++t) {
+        const hipError_t e = launch_seed_iteration(s, st);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_pair_scalars(const SolveDev &s, hipStream_t st)

@@ -84,6 +84,20 @@ struct HubbardOp {
     int32_t pad;
 };
 
+// Stored matrices of at most SEED_BLOCK_ROWS rows run a block's seed iterations in one launch, one
+// workgroup per right-hand side (seed_block.hip).  Larger ones, up to the 8192 rows whose p fits in
+// LDS (128 of 160 KB), do so from SEED_BLOCK_RHS right-hand sides on: there one workgroup
+// streams a matrix of over half a megabyte through its L2 port each iteration, which takes longer
+// than the five launches for one right-hand side (cubic 20^3: 20 against 16 us) but the same
+// time for up to 256 of them (23 against 60 us at 128).
+static constexpr int64_t SEED_BLOCK_ROWS = 4096;
+static constexpr int64_t SEED_BLOCK_ROWS_MANY = 8192;
+static constexpr int64_t SEED_BLOCK_RHS = 128;
+inline bool seed_block_fits(int64_t n, int64_t K)
+{
+    return n <= SEED_BLOCK_ROWS || (n <= SEED_BLOCK_ROWS_MANY && K >= SEED_BLOCK_RHS);
+}
+
 // Right-hand sides of at least this many rows sum their seed reductions with 1024 threads.
 static constexpr int64_t RED_BIG_ROWS = 1 << 21;
 
@@ -177,6 +191,8 @@ struct SolveDev {
     double *coefx;             // [6 TB + 4][K*M] expanded weights of this block, pair fastest (double-buffered
                                // like coef): per step s (Re c_s, Im c_s, Re c_s + Im c_s, Re d_s, Im d_s,
                                // Re d_s + Im d_s), then gamma (re, im), delta (re, im)
+    int seed_block;            // 1: the block's seed iterations run in one launch (see seed_block.hip)
+    int max_w;                 // widest matrix slice over the right-hand sides
     int has_sell, has_hub;     // some rhs has a stored matrix / a matrix-free Hubbard operator
     int hub_lds;               // every Hubbard operator's down-spin block fits the LDS-tiled product
     int has_red_small, has_red_big; // some rhs below / at or above 2^21 rows (per-rhs reduction width)
@@ -214,6 +230,10 @@ hipError_t launch_init(const SolveDev &s, const double2 *B, const int64_t *unit_
                        const int32_t *seed_idx, int32_t limit, hipStream_t st);
 // one seed iteration (four launches, see kernels.hip)
 hipError_t launch_seed_iteration(const SolveDev &s, hipStream_t st);
+// the block's TB seed iterations in one launch (s.seed_block)
+hipError_t launch_seed_block(const SolveDev &s, hipStream_t st);
+// the block's TB seed iterations, in whichever form s asks for
+hipError_t launch_block_iterations(const SolveDev &s, hipStream_t st);
 hipError_t launch_pair_scalars(const SolveDev &s, hipStream_t st);
 hipError_t launch_flush(const SolveDev &s, hipStream_t st);
 hipError_t launch_block_finalize(const SolveDev &s, hipStream_t st);
