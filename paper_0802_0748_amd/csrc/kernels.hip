@@ -889,7 +889,7 @@ __global__ void __launch_bounds__(NT) k_beta(SolveDev s)
 }
 
 // ---------------------------------------------------------------------------------------
-// shift scalars for the steps of the finished block (one thread per (rhs, shift) pair):
+// shift scalars for the steps of the finished block, per (rhs, shift) pair:
 //   pi_{n+1} = (1 + alpha_n sigma) pi_n + (alpha_n beta_{n-1} / alpha_{n-1}) (pi_n - pi_{n-1})
 //   alpha^k_n = (pi_n / pi_{n+1}) alpha_n,  beta^k_n = (pi_n / pi_{n+1})^2 beta_n
 // Convergence of the pair: ||r_{n+1}|| / (|pi_{n+1}| ||b||) < tol.
@@ -898,95 +898,187 @@ __global__ void __launch_bounds__(NT) k_beta(SolveDev s)
 //   u^k_n = r_n + b'_n u^k_{n-1},   x^k_{n+1} = x^k_n + a'_n u^k_n,
 //   a'_n = alpha^k_n / pi_n = alpha_n / pi_{n+1},
 //   b'_n = beta^k_{n-1} pi_n / pi_{n-1} = beta_{n-1} pi_{n-1} / pi_n
-// (two complex multiply-adds per step instead of three for p^k directly).  This thread
+// (two complex multiply-adds per step instead of three for p^k directly).  The kernel
 // writes (a'_n, b'_n) for every step of the block in which the pair is still active.
+//
+// A workgroup of 16 P threads takes P shifts of one rhs.  Only the recurrence of pi is serial: P
+// lanes run it over the block (about five dependent operations a step, pi_n kept in LDS), and
+// everything that hangs off it (the residual and the stopping test, the quotients and (a'_n, b'_n))
+// is one item per pair and step over all threads, written with consecutive steps in consecutive
+// lanes.  beta_{n-1} / alpha_{n-1} is the rhs's own and formed once per step, and pi_{n-1} / pi_n is
+// one step's quotient of the next.  One thread per pair, with the four divisions of a step in the
+// chain, took 55-65 us for any number of pairs up to a few thousand; this takes 7-9 us (P = 16),
+// P = 64 keeps the statistics' atomics few when there are tens of thousands of pairs.
+// Roundings are written out (cmul_f, cdiv_f): those of the expressions above.
 // ---------------------------------------------------------------------------------------
-template <typename V>
-__device__ inline unsigned long long pair_scalars_one(const SolveDev &s, int64_t pair, unsigned long long &flops)
+static constexpr int PS_STEPS = 48;  // longest block
+
+template <typename V, int P>
+__global__ void __launch_bounds__(P == 16 ? 256 : 512) k_pair_scalars(SolveDev s)
 {
-    flops = 0ull;
-    const int64_t j = pair / s.M, k = pair % s.M;
+    constexpr int NT = P == 16 ? 256 : 512;
+    __shared__ double2 pin[PS_STEPS + 2][P + 1];  // pi_{n0-1}, pi_{n0}, pi_{n0+1} ... per pair
+    __shared__ double2 ha[PS_STEPS], hb[PS_STEPS], hc[PS_STEPS], hs[PS_STEPS];
+    __shared__ double hr[PS_STEPS];
+    __shared__ int stop[P];  // first step that ends the pair: 2 t (pi = 0), 2 t + 1 (converged)
+    __shared__ int live[P];
+    __shared__ unsigned long long st_bytes, st_flops;
+    __shared__ unsigned int st_count;
+    const int64_t per = (s.M + P - 1) / P;
+    const int64_t j = blockIdx.x / per;
+    const int64_t k0 = (blockIdx.x - j * per) * P;
+    const int64_t p0 = j * s.M + k0;  // first pair
+    const int tid = threadIdx.x;
+    const int npair = (int)min((int64_t)P, s.M - k0);
     const SeedState st = s.seed[j];
     const int ns = st.step;
-    if (!s.active[pair] || ns == 0) {
-        s.nact[pair] = 0;
-        return 0ull;
+    if (k0 == 0 && tid == 0) {
+        // what the deferred update of this block needs, fixed before the block ends
+        s.blk[4 * j + 0] = st.step;
+        s.blk[4 * j + 1] = st.base;
+        s.blk[4 * j + 2] = st.iter == st.step ? 1 : 0;
     }
-    const double2 sig = csub(s.z[s.zper ? j : k], st.zs);
-    double2 ap = st.a0, bp = st.b0;
-    double2 pi = s.pi[pair], pip = s.pi_prev[pair], bk = s.beta_k[pair];
-    double res = s.res[pair];
-    int act = 1, status = s.pstatus[pair], na = 0, iters = s.iters[pair];
-    V *cf = (V *)s.coef + pair * (int64_t)s.TB * 2;
-    for (int t = 0; t < ns; ++t) {
-        const double2 a = s.ahist[j * s.TB + t];
-        const double2 b = s.bhist[j * s.TB + t];
-        const double2 c1 = cmul(cadd(cmk(1, 0), cmul(a, sig)), pi);
-        const double2 c2 = cmul(cdiv(cmul(a, bp), ap), csub(pi, pip));
-        const double2 pin = cadd(c1, c2);
-        if (cis0(pin)) {
-            status = PAIR_BREAKDOWN;
-            act = 0;
-            break;
-        }
-        const double2 ratio = cdiv(pi, pin);
-        cf[2 * t + 0] = to_v<V>(cdiv(a, pin));
-        cf[2 * t + 1] = to_v<V>(cmul(bp, cdiv(pip, pi)));
-        bk = cmul(cmul(ratio, ratio), b);
-        pip = pi;
-        pi = pin;
-        na = t + 1;
-        iters = st.iter - ns + t + 1;
-        res = s.rnhist[j * s.TB + t] / (sqrt(cabs2(pi)) * st.nb);
-        ap = a;
-        bp = b;
-        if (!s.fixed && res < s.tol) {
-            act = 0;
-            status = PAIR_OK;
-            break;
+    if (ns == 0) {
+        if (tid < npair) s.nact[p0 + tid] = 0;
+        return;
+    }
+    const bool row_proj = s.wslot && !s.wproj;  // pairs without a stored direction follow the kept row
+    if (tid < ns) {
+        const double2 a = s.ahist[j * s.TB + tid];
+        ha[tid] = a;
+        hb[tid] = s.bhist[j * s.TB + tid];
+        hr[tid] = s.rnhist[j * s.TB + tid];
+        const double2 ap = tid ? s.ahist[j * s.TB + tid - 1] : st.a0;
+        const double2 bp = tid ? s.bhist[j * s.TB + tid - 1] : st.b0;
+        hc[tid] = cdiv_f(cmul_f(a, bp), ap);
+        if (s.wproj) hs[tid] = s.shist[j * s.TB + tid];
+        else if (row_proj)
+            hs[tid] = s.ring[(int64_t)((st.base + tid) % s.R) * s.ntot + s.desc[j].voff + s.proj_row[j]];
+    }
+    if (tid < P) {
+        const bool on = tid < npair && s.active[p0 + tid];
+        live[tid] = on ? 1 : 0;
+        stop[tid] = 2 * ns;
+        if (tid < npair && !on) s.nact[p0 + tid] = 0;
+        if (on) {
+            pin[0][tid] = s.pi_prev[p0 + tid];
+            pin[1][tid] = s.pi[p0 + tid];
         }
     }
-    s.pi[pair] = pi;
-    s.pi_prev[pair] = pip;
-    s.beta_k[pair] = bk;
-    s.res[pair] = res;
-    s.iters[pair] = iters;
-    s.pstatus[pair] = status;
-    s.active[pair] = act;
-    s.nact[pair] = na;
-    if (na == 0) return 0ull;
-    if (s.wproj) {
+    if (tid == 0) {
+        st_bytes = 0ull;
+        st_flops = 0ull;
+        st_count = 0u;
+    }
+    __syncthreads();
+    if (tid < npair && live[tid]) {
+        const double2 sig = csub(s.z[s.zper ? j : k0 + tid], st.zs);
+        double2 pp = pin[0][tid], pi = pin[1][tid];
+        for (int t = 0; t < ns; ++t) {
+            const double2 f = cmul_f(ha[t], sig);
+            const double2 c1 = cmul_f(make_double2(1.0 + f.x, 0.0 + f.y), pi);
+            const double2 c2 = cmul_f(hc[t], make_double2(pi.x - pp.x, pi.y - pp.y));
+            pp = pi;
+            pi = make_double2(c1.x + c2.x, c1.y + c2.y);
+            pin[t + 2][tid] = pi;
+        }
+    }
+    __syncthreads();
+    auto res_of = [&](double2 p, int t) -> double { return hr[t] / (sqrt(fma(p.x, p.x, p.y * p.y)) * st.nb); };
+    for (int i = tid; i < npair * ns; i += NT) {
+        const int q = i / ns, t = i - q * ns;
+        if (!live[q]) continue;
+        const double2 p = pin[t + 2][q];
+        if (cis0(p)) atomicMin(&stop[q], 2 * t);
+        else if (!s.fixed && res_of(p, t) < s.tol) atomicMin(&stop[q], 2 * t + 1);
+    }
+    __syncthreads();
+    const int TB = s.TB;
+    for (int i = tid; i < npair * TB; i += NT) {
+        const int q = i / TB, t = i - q * TB;
+        if (!live[q]) continue;
+        const int64_t pair = p0 + q;
+        const int na = (stop[q] + 1) >> 1;  // steps the pair takes
+        V *cf = (V *)s.coef + (pair * TB + t) * 2;
+        if (t < na) {
+            const double2 pp = pin[t][q], pi = pin[t + 1][q], pn = pin[t + 2][q];
+            const double2 bp = t ? hb[t - 1] : st.b0;
+            cf[0] = to_v<V>(cdiv_f(ha[t], pn));
+            cf[1] = to_v<V>(cmul_f(cdiv_f(pp, pi), bp));
+        } else {
+            // Steps past the pair's last one are padded with a' = 0, b' = 1, which leaves x_k
+            // unchanged (and u_k too while the residual history is zero there), so the deferred
+            // update runs every step without a per-pair branch.
+            cf[0] = to_v<V>(cmk(0, 0));
+            cf[1] = to_v<V>(cmk(1, 0));
+        }
+        if (t == na - 1) {
+            const double2 pi = pin[t + 1][q], pn = pin[t + 2][q];
+            const double2 ra = cdiv_f(pi, pn);
+            const double xy = ra.x * ra.y;
+            s.pi[pair] = pn;
+            s.pi_prev[pair] = pi;
+            s.beta_k[pair] = cmul_f(make_double2(fma(ra.x, ra.x, -(ra.y * ra.y)), xy + xy), hb[t]);
+            s.res[pair] = res_of(pn, t);
+            s.iters[pair] = st.iter - ns + na;
+        }
+        if (t == 0) {
+            const bool ended = stop[q] < 2 * ns;
+            if (ended) {
+                s.pstatus[pair] = (stop[q] & 1) ? PAIR_OK : PAIR_BREAKDOWN;
+                s.active[pair] = 0;
+            }
+            s.nact[pair] = na;
+            if (na > 0 && !(s.wslot && s.wslot[pair] < 0)) {
+                // algorithmic bytes of this pair's deferred update: u_k (and x_k unless projected)
+                // written once, and read once unless this is the first block; flops: the pair's own
+                // steps (not the padding), two complex multiply-adds (16 flops) per row and step, one
+                // (8) where only u_k is stored
+                const unsigned long long esz = s.precision == 0 ? 16ull : 8ull;
+                const unsigned long long nv = s.X ? 2ull : 1ull;
+                const unsigned long long rw = (st.iter - ns == 0) ? 1ull : 2ull;
+                const unsigned long long n = (unsigned long long)s.desc[j].n;
+                atomicAdd(&st_bytes, nv * rw * esz * n);
+                atomicAdd(&st_flops, (unsigned long long)na * 8ull * nv * n);
+                atomicAdd(&st_count, 1u);
+            }
+        }
+    }
+    __syncthreads();
+    if (tid == 0 && st_count > 0) {
+        atomicAdd(&s.stats[0], st_bytes);
+        atomicAdd(&s.stats[1], (unsigned long long)st_count);
+        atomicAdd(&s.stats[2], st_flops);
+    }
+    if (tid >= npair || !live[tid]) return;
+    const int64_t pair = p0 + tid;
+    const int na = (stop[tid] + 1) >> 1;
+    if (na == 0) return;
+    const V *cf = (const V *)s.coef + pair * (int64_t)TB * 2;
+    if (s.wproj || (row_proj && s.wslot[pair] < 0)) {
         // vector projection: <w|x_k> and <w|u_k> of every pair follow the block's steps with
-        // s_t = w . r_t in place of r_t (the update is linear); a stored direction still
-        // gets its full u_k below, for a seed switch
+        // s_t = w . r_t in place of r_t (the update is linear; a stored direction still gets its
+        // full u_k, for a seed switch).  No stored direction: x_k and u_k at the kept row alone.
+        // Either way the arithmetic is the deferred update's.
         V x = to_v<V>(s.Xproj[pair]), u = to_v<V>(s.Uproj[pair]);
-        for (int t = 0; t < na; ++t) {
-            u = cfma(cf[2 * t + 1], u, to_v<V>(s.shist[j * s.TB + t]));
-            x = cfma(cf[2 * t + 0], u, x);
+        constexpr int CH = 8;
+        for (int t0 = 0; t0 < na; t0 += CH) {
+            V a[CH], b[CH];
+#pragma unroll
+            for (int c = 0; c < CH; ++c) {
+                const int t = t0 + c < TB ? t0 + c : TB - 1;
+                a[c] = cf[2 * t + 0];
+                b[c] = cf[2 * t + 1];
+            }
+#pragma unroll
+            for (int c = 0; c < CH; ++c) {
+                if (t0 + c >= na) break;
+                u = cfma(b[c], u, to_v<V>(hs[t0 + c]));
+                x = cfma(a[c], u, x);
+            }
         }
         s.Xproj[pair] = make_double2((double)x.x, (double)x.y);
         s.Uproj[pair] = make_double2((double)u.x, (double)u.y);
-        if (s.wslot && s.wslot[pair] < 0) return 0ull;
-    } else if (s.wslot && s.wslot[pair] < 0) {
-        // no stored direction: carry x_k and u_k at the kept row only, with the same
-        // arithmetic the deferred update applies to a stored direction
-        const int64_t at = s.desc[j].voff + s.proj_row[j];
-        V x = to_v<V>(s.Xproj[pair]), u = to_v<V>(s.Uproj[pair]);
-        for (int t = 0; t < na; ++t) {
-            const V r = to_v<V>(s.ring[(int64_t)((st.base + t) % s.R) * s.ntot + at]);
-            u = cfma(cf[2 * t + 1], u, r);
-            x = cfma(cf[2 * t + 0], u, x);
-        }
-        s.Xproj[pair] = make_double2((double)x.x, (double)x.y);
-        s.Uproj[pair] = make_double2((double)u.x, (double)u.y);
-        return 0ull;
-    }
-    // Steps past the pair's last one are padded with a' = 0, b' = 1, which leaves x_k
-    // unchanged (and u_k too while the residual history is zero there), so the deferred
-    // update runs every step without a per-pair branch.
-    for (int t = na; t < s.TB; ++t) {
-        cf[2 * t + 0] = to_v<V>(cmk(0, 0));
-        cf[2 * t + 1] = to_v<V>(cmk(1, 0));
     }
     if (sizeof(V) == sizeof(double2) && s.expanded) {
         // The block's steps unrolled (u_in, x_in the values at the block's start):
@@ -1021,50 +1113,6 @@ __device__ inline unsigned long long pair_scalars_one(const SolveDev &s, int64_t
         e[1 * KM] = gam.y;
         e[2 * KM] = del.x;
         e[3 * KM] = del.y;
-    }
-    // algorithmic bytes of this pair's deferred update: u_k (and x_k unless projected)
-    // written once, and read once unless this is the first block
-    const unsigned long long esz = s.precision == 0 ? 16ull : 8ull;
-    const unsigned long long nv = s.X ? 2ull : 1ull;
-    const unsigned long long rw = (st.iter - ns == 0) ? 1ull : 2ull;
-    // algorithmic flops: the pair's own steps (not the padding), two complex multiply-adds
-    // (16 flops) per row and step, one (8) where only u_k is stored
-    flops = (unsigned long long)na * 8ull * nv * (unsigned long long)s.desc[j].n;
-    return nv * rw * esz * (unsigned long long)s.desc[j].n;
-}
-
-template <typename V>
-__global__ void __launch_bounds__(WG) k_pair_scalars(SolveDev s)
-{
-    __shared__ unsigned long long shb[WG], shf[WG];
-    __shared__ unsigned int shc[WG];
-    const int64_t pair = (int64_t)blockIdx.x * WG + threadIdx.x;
-    if (pair < s.K * s.M && pair % s.M == 0) {
-        // what the deferred update of this block needs, fixed before the block ends
-        const int64_t j = pair / s.M;
-        const SeedState st = s.seed[j];
-        s.blk[4 * j + 0] = st.step;
-        s.blk[4 * j + 1] = st.base;
-        s.blk[4 * j + 2] = st.iter == st.step ? 1 : 0;
-    }
-    unsigned long long f = 0ull;
-    const unsigned long long b = pair < s.K * s.M ? pair_scalars_one<V>(s, pair, f) : 0ull;
-    shb[threadIdx.x] = b;
-    shf[threadIdx.x] = b > 0 ? f : 0ull;
-    shc[threadIdx.x] = b > 0 ? 1u : 0u;
-    __syncthreads();
-    for (int h = WG / 2; h > 0; h >>= 1) {
-        if ((int)threadIdx.x < h) {
-            shb[threadIdx.x] += shb[threadIdx.x + h];
-            shf[threadIdx.x] += shf[threadIdx.x + h];
-            shc[threadIdx.x] += shc[threadIdx.x + h];
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0 && shc[0] > 0) {
-        atomicAdd(&s.stats[0], shb[0]);
-        atomicAdd(&s.stats[1], (unsigned long long)shc[0]);
-        atomicAdd(&s.stats[2], shf[0]);
     }
 }
 
@@ -1628,10 +1676,16 @@ hipError_t launch_block_iterations(const SolveDev &s, hipStream_t st)
 
 hipError_t launch_pair_scalars(const SolveDev &s, hipStream_t st)
 {
-    const int64_t KM = s.K * s.M;
-    const dim3 g((unsigned)((KM + WG - 1) / WG));
-    if (s.precision == 0) hipLaunchKernelGGL(k_pair_scalars<double2>, g, dim3(WG), 0, st, s);
-    else hipLaunchKernelGGL(k_pair_scalars<float2>, g, dim3(WG), 0, st, s);
+    // 16 shifts per workgroup until there are enough workgroups for the chip several times over
+    const bool wide = s.K * ((s.M + 15) / 16) > 1024;
+    const dim3 g((unsigned)(s.K * ((s.M + (wide ? 63 : 15)) / (wide ? 64 : 16))));
+    if (wide) {
+        if (s.precision == 0) hipLaunchKernelGGL((k_pair_scalars<double2, 64>), g, dim3(512), 0, st, s);
+        else hipLaunchKernelGGL((k_pair_scalars<float2, 64>), g, dim3(512), 0, st, s);
+    } else {
+        if (s.precision == 0) hipLaunchKernelGGL((k_pair_scalars<double2, 16>), g, dim3(256), 0, st, s);
+        else hipLaunchKernelGGL((k_pair_scalars<float2, 16>), g, dim3(256), 0, st, s);
+    }
     return hipGetLastError();
 }
 
