@@ -1254,6 +1254,8 @@ __global__ void __launch_bounds__(WG) k_block_finalize(SolveDev s)
 // Vectors of a seed switch to shift t after step n: r <- r / pi_t(n+1); the stored scaled
 // directions of the active pairs move to the new seed's scale, u_k <- u_k / pi_t(n); the new
 // seed's direction is p <- p_t(n) = u_t / pi_t(n); rho <- r.r.
+static constexpr int SWITCH_CHUNK = 8;
+
 template <typename V>
 __global__ void __launch_bounds__(WG) k_switch_vectors(SolveDev s)
 {
@@ -1273,13 +1275,28 @@ __global__ void __launch_bounds__(WG) k_switch_vectors(SolveDev s)
         V *P = (V *)s.P + s.Mst * d.voff;
         const V sc = to_v<V>(st.inv_ppt);
         const V zero = to_v<V>(cmk(0, 0));
-        for (int64_t w = 0; w < s.Mst; ++w) {
-            const int64_t k = s.wshift ? s.wshift[j * s.Mst + w] : w;
-            if (!s.active[j * s.M + k]) continue;
-            V *up = P + w * d.n + row;
-            const V u = cfma(sc, *up, zero);
-            *up = u;
-            if (k == st.sw_target) s.p[p_index(s, j, d, row)] = make_double2((double)u.x, (double)u.y);
+        // SWITCH_CHUNK stored directions at a time: their loads are in flight together (one by one a
+        // row's 128 directions took 128 round trips, 100 us; now 20)
+        for (int64_t w0 = 0; w0 < s.Mst; w0 += SWITCH_CHUNK) {
+            bool on[SWITCH_CHUNK], seed[SWITCH_CHUNK];
+            V u[SWITCH_CHUNK];
+#pragma unroll
+            for (int c = 0; c < SWITCH_CHUNK; ++c) {
+                const int64_t w = w0 + c;
+                const int64_t k = w < s.Mst ? (s.wshift ? s.wshift[j * s.Mst + w] : w) : 0;
+                on[c] = w < s.Mst && s.active[j * s.M + k];
+                seed[c] = k == st.sw_target;
+            }
+#pragma unroll
+            for (int c = 0; c < SWITCH_CHUNK; ++c)
+                if (on[c]) u[c] = P[(w0 + c) * d.n + row];
+#pragma unroll
+            for (int c = 0; c < SWITCH_CHUNK; ++c) {
+                if (!on[c]) continue;
+                const V v = cfma(sc, u[c], zero);
+                P[(w0 + c) * d.n + row] = v;
+                if (seed[c]) s.p[p_index(s, j, d, row)] = make_double2((double)v.x, (double)v.y);
+            }
         }
         rr = cmul(r, r);
     }
@@ -1418,6 +1435,8 @@ __global__ void k_gather_diag(const RhsDesc *__restrict__ desc, int64_t K, int64
     G[k * K + j] = Xproj ? Xproj[pair] : X[M * desc[j].voff + k * desc[j].n + rows[j]];
 }
 
+static constexpr int RHO_CHUNK = 16;
+
 // Density matrix, band energy and energy gradient of one batch of columns.
 //   rho[(a, b)] += Re sum_k w_k x_{j,k}[a]     for the stored entries (a, b) of column b = cols_of_rhs[j]
 //   Epart[j] = Re sum_k w_k z_k x_{j,k}[b]
@@ -1433,33 +1452,63 @@ __global__ void k_density_rho(int64_t n, int64_t K, int64_t M, const double2 *__
     const int64_t j = blockIdx.x;
     const int64_t b = cols_of_rhs[j];
     const int64_t e0 = row_ptr[b], e1 = row_ptr[b + 1];
-    for (int64_t e = e0 + threadIdx.x; e < e1; e += blockDim.x) {
+    // the first wave takes the column's entries, the second one its energy
+    if (threadIdx.x < 64)
+    for (int64_t e = e0 + threadIdx.x; e < e1; e += 64) {
         const int64_t a = col[e];
         double acc = 0;
-        for (int64_t k = 0; k < M; ++k) {
+        // the nodes in order, the loads of RHO_CHUNK of them in flight together
+        int64_t k = 0;
+        for (; k + RHO_CHUNK <= M; k += RHO_CHUNK) {
+            double2 x[RHO_CHUNK];
+#pragma unroll
+            for (int c = 0; c < RHO_CHUNK; ++c) x[c] = X[(j * M + k + c) * n + a];
+#pragma unroll
+            for (int c = 0; c < RHO_CHUNK; ++c) acc += w[k + c].x * x[c].x - w[k + c].y * x[c].y;
+        }
+        for (; k < M; ++k) {
             const double2 x = X[(j * M + k) * n + a];
             acc += w[k].x * x.x - w[k].y * x.y;
         }
         if (rho) rho[mirror[e]] += acc;
     }
-    if (threadIdx.x == 0) {
+    if (threadIdx.x == 64) {
         double acc = 0;
-        for (int64_t k = 0; k < M; ++k) {
+        int64_t k = 0;
+        for (; k + RHO_CHUNK <= M; k += RHO_CHUNK) {
+            double2 x[RHO_CHUNK];
+#pragma unroll
+            for (int c = 0; c < RHO_CHUNK; ++c) x[c] = X[(j * M + k + c) * n + b];
+#pragma unroll
+            for (int c = 0; c < RHO_CHUNK; ++c) {
+                const double2 wz = cmul_f(z[k + c], w[k + c]);
+                acc += wz.x * x[c].x - wz.y * x[c].y;
+            }
+        }
+        for (; k < M; ++k) {
             const double2 x = X[(j * M + k) * n + b];
-            const double2 wz = cmul(w[k], z[k]);
+            const double2 wz = cmul_f(z[k], w[k]);
             acc += wz.x * x.x - wz.y * x.y;
         }
         Epart[j] = acc;
     }
 }
 
-__global__ void k_sum_into(const double *__restrict__ part, int64_t count, double *__restrict__ out)
+// One sum in index order, by the first lane: the wave loads 64 terms at once into LDS.
+__global__ void __launch_bounds__(64) k_sum_into(const double *__restrict__ part, int64_t count, double *__restrict__ out)
 {
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        double acc = 0;
-        for (int64_t i = 0; i < count; ++i) acc += part[i];
-        out[0] += acc;
+    __shared__ double sh[64];
+    double acc = 0;
+    for (int64_t i0 = 0; i0 < count; i0 += 64) {
+        sh[threadIdx.x] = i0 + threadIdx.x < count ? part[i0 + threadIdx.x] : 0.0;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            const int m = (int)min((int64_t)64, count - i0);
+            for (int i = 0; i < m; ++i) acc += sh[i];
+        }
+        __syncthreads();
     }
+    if (threadIdx.x == 0) out[0] += acc;
 }
 
 // Partial sums of the pair contraction Re sum_p c_p x_p[a] x_p[b] over the stored entries
@@ -1507,13 +1556,27 @@ __global__ void __launch_bounds__(WG) k_pair_outer(int64_t n, int64_t npairs, in
         if (i < w) out[i] = acc[i];
 }
 
-// grad[e] += sum over chunks, in chunk order
-__global__ void k_chunk_sum(int64_t nnz, int64_t nchunk, const double *__restrict__ part, double *__restrict__ grad)
+// grad[e] += sum over chunks, in chunk order.  A few thousand entries with up to 2048 chunks each
+// (small matrices) are one chain of additions per entry: CSUM loads are in flight per thread, and
+// a wave is a workgroup so that a small matrix still covers many compute units (one load per
+// round trip took 490 us for 2048 chunks of 2176 entries, now about 30).
+static constexpr int CSUM = 64;
+
+__global__ void __launch_bounds__(64) k_chunk_sum(int64_t nnz, int64_t nchunk, const double *__restrict__ part,
+                                                  double *__restrict__ grad)
 {
-    const int64_t e = (int64_t)blockIdx.x * WG + threadIdx.x;
+    const int64_t e = (int64_t)blockIdx.x * 64 + threadIdx.x;
     if (e >= nnz) return;
     double acc = 0;
-    for (int64_t c = 0; c < nchunk; ++c) acc += part[c * nnz + e];
+    int64_t c = 0;
+    for (; c + CSUM <= nchunk; c += CSUM) {
+        double v[CSUM];
+#pragma unroll
+        for (int u = 0; u < CSUM; ++u) v[u] = part[(c + u) * nnz + e];
+#pragma unroll
+        for (int u = 0; u < CSUM; ++u) acc += v[u];
+    }
+    for (; c < nchunk; ++c) acc += part[c * nnz + e];
     grad[e] += acc;
 }
 
@@ -1768,7 +1831,7 @@ hipError_t launch_density_rho(int64_t n, int64_t K, int64_t M, const double2 *X,
                               const int64_t *row_ptr, const int32_t *col, const int32_t *mirror, const double2 *w,
                               const double2 *z, double *rho, double *Epart, double *Eacc, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_density_rho, dim3((unsigned)K), dim3(64), 0, st, n, K, M, X, cols_of_rhs, row_ptr, col,
+    hipLaunchKernelGGL(k_density_rho, dim3((unsigned)K), dim3(128), 0, st, n, K, M, X, cols_of_rhs, row_ptr, col,
                        mirror, w, z, rho, Epart);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -1827,7 +1890,7 @@ hipError_t launch_pair_outer(int64_t n, int64_t npairs, const double2 *X, const 
         hipLaunchKernelGGL(k_pair_outer<32>, g, dim3(WG), 0, st, n, npairs, pch, X, c, row_ptr, col, nnz, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_chunk_sum, dim3((unsigned)((nnz + WG - 1) / WG)), dim3(WG), 0, st, nnz, nchunk,
+    hipLaunchKernelGGL(k_chunk_sum, dim3((unsigned)((nnz + 63) / 64)), dim3(64), 0, st, nnz, nchunk,
                        (const double *)part, grad);
     return hipGetLastError();
 }
