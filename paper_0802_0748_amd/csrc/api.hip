@@ -61,26 +61,167 @@ static bool device_ok(const void *p)
         if (e_ != hipSuccess) return fail(SCOCG_EHIP, std::string(#expr) + ": " + hipGetErrorString(e_)); \
     } while (0)
 
+// Work buffers of 1 to 256 MiB are kept when a call ends and handed to the next one that asks for
+// about their size: freeing and allocating them again took 1.3 of the 3.1 ms of a 128-row energy
+// with gradient (hipFree 1.0 ms, hipMalloc 0.3 ms; smaller blocks cost half a microsecond, and
+// beyond 256 MiB a call's own time hides it).  At most KEEP_BYTES stay, the oldest go first; all go
+// when the last matrix (or tape) is released or an allocation fails.  A block comes back only after
+// the stream of its call has drained, so whoever takes it next, on any thread or stream, finds
+// it idle; contents are never relied on.
+class Keeper {
+public:
+    static constexpr size_t KEEP_MIN = 1ull << 20, KEEP_MAX = 256ull << 20, KEEP_BYTES = 1ull << 30;
+    static bool keeps(size_t bytes) { return bytes >= KEEP_MIN && bytes <= KEEP_MAX; }
+    hipError_t take(size_t bytes, void **ptr, size_t *got, int *dev)
+    {
+        hipError_t e = hipGetDevice(dev);
+        if (e != hipSuccess) return e;
+        {
+            std::lock_guard<std::mutex> lock(mu_);
+            size_t best = free_.size();
+            for (size_t i = 0; i < free_.size(); ++i)
+                if (free_[i].dev == *dev && free_[i].bytes >= bytes && free_[i].bytes <= bytes + bytes / 4 &&
+                    (best == free_.size() || free_[i].bytes < free_[best].bytes))
+                    best = i;
+            if (best < free_.size()) {
+                *ptr = free_[best].ptr;
+                *got = free_[best].bytes;
+                held_ -= *got;
+                free_.erase(free_.begin() + best);
+                return hipSuccess;
+            }
+        }
+        *got = bytes;
+        return fresh(bytes, ptr);
+    }
+    // hipMalloc, once more without the kept blocks if it fails
+    hipError_t fresh(size_t bytes, void **ptr)
+    {
+        hipError_t e = hipMalloc(ptr, bytes);
+        if (e != hipSuccess && drop()) {
+            (void)hipGetLastError();
+            e = hipMalloc(ptr, bytes);
+        }
+        return e;
+    }
+    void give(void *ptr, size_t bytes, int dev)
+    {
+        std::vector<void *> out;
+        {
+            std::lock_guard<std::mutex> lock(mu_);
+            if (live_ == 0) {
+                out.push_back(ptr);
+            } else {
+                free_.push_back({ptr, bytes, dev});
+                held_ += bytes;
+                while (held_ > KEEP_BYTES) {
+                    out.push_back(free_.front().ptr);
+                    held_ -= free_.front().bytes;
+                    free_.erase(free_.begin());
+                }
+            }
+        }
+        for (void *q : out) (void)hipFree(q);
+    }
+    void *take_pinned(size_t bytes)
+    {
+        std::lock_guard<std::mutex> lock(mu_);
+        for (size_t i = 0; i < pinned_.size(); ++i)
+            if (pinned_[i].bytes == bytes) {
+                void *q = pinned_[i].ptr;
+                pinned_.erase(pinned_.begin() + i);
+                return q;
+            }
+        return nullptr;
+    }
+    bool give_pinned(void *ptr, size_t bytes)
+    {
+        std::lock_guard<std::mutex> lock(mu_);
+        if (live_ == 0 || pinned_.size() >= 8 || bytes > (4ull << 20)) return false;
+        pinned_.push_back({ptr, bytes, 0});
+        return true;
+    }
+    bool drop()
+    {
+        std::vector<Block> out, host;
+        {
+            std::lock_guard<std::mutex> lock(mu_);
+            out.swap(free_);
+            host.swap(pinned_);
+            held_ = 0;
+        }
+        for (const Block &b : out) (void)hipFree(b.ptr);
+        for (const Block &b : host) (void)hipHostFree(b.ptr);
+        return !out.empty();
+    }
+    void matrix_up()
+    {
+        std::lock_guard<std::mutex> lock(mu_);
+        ++live_;
+    }
+    void matrix_down()
+    {
+        bool last;
+        {
+            std::lock_guard<std::mutex> lock(mu_);
+            last = --live_ == 0;
+        }
+        if (last) drop();
+    }
+
+private:
+    struct Block {
+        void *ptr;
+        size_t bytes;
+        int dev;
+    };
+    std::mutex mu_;
+    std::vector<Block> free_, pinned_;
+    size_t held_ = 0;
+    int64_t live_ = 0;  // uploaded matrices
+};
+// (never destroyed: buffers of static objects may outlive it otherwise)
+Keeper &keeper()
+{
+    static Keeper *k = new Keeper;
+    return *k;
+}
+// the stream of the call in progress on this thread: its work buffers are idle once it has drained
+thread_local hipStream_t g_call_stream = nullptr;
+
 // Device allocations released when the owner goes out of scope.
 struct DevBuf {
     void *ptr = nullptr;
     size_t bytes = 0;
+    size_t kept = 0;  // size of the block if it goes back to the keeper
+    int dev = 0;
     DevBuf() = default;
     DevBuf(const DevBuf &) = delete;
     DevBuf &operator=(const DevBuf &) = delete;
     ~DevBuf() { release(); }
     void release()
     {
-        if (ptr) (void)hipFree(ptr);
+        if (ptr && kept && hipStreamSynchronize(g_call_stream) == hipSuccess) keeper().give(ptr, kept, dev);
+        else if (ptr) (void)hipFree(ptr);
         ptr = nullptr;
         bytes = 0;
+        kept = 0;
     }
+    // for the length of the caller's life (a tape's solutions)
     hipError_t alloc(size_t b)
     {
         release();
         bytes = b;
         if (b == 0) return hipSuccess;
-        return hipMalloc(&ptr, b);
+        return keeper().fresh(b, &ptr);
+    }
+    // for the length of a call on g_call_stream
+    hipError_t work(size_t b)
+    {
+        if (!Keeper::keeps(b)) return alloc(b);
+        release();
+        bytes = b;
+        return keeper().take(b, &ptr, &kept, &dev);
     }
     template <typename T>
     T *as() const { return (T *)ptr; }
@@ -120,13 +261,23 @@ struct GraphPair {
     }
 };
 
+// Pinned host memory of a call on g_call_stream (its allocation and release take 60 us): sizes are
+// rounded up to a power of two, and up to 8 blocks of at most 4 MiB are kept as the work buffers are.
 struct PinnedBuf {
     void *ptr = nullptr;
+    size_t bytes = 0;
     ~PinnedBuf()
     {
-        if (ptr) (void)hipHostFree(ptr);
+        if (!ptr) return;
+        if (hipStreamSynchronize(g_call_stream) != hipSuccess || !keeper().give_pinned(ptr, bytes)) (void)hipHostFree(ptr);
     }
-    hipError_t alloc(size_t b) { return hipHostMalloc(&ptr, b, hipHostMallocDefault); }
+    hipError_t alloc(size_t b)
+    {
+        bytes = 4096;
+        while (bytes < b) bytes *= 2;
+        ptr = keeper().take_pinned(bytes);
+        return ptr ? hipSuccess : hipHostMalloc(&ptr, bytes, hipHostMallocDefault);
+    }
 };
 
 }  // namespace
@@ -291,6 +442,7 @@ extern "C" int csr_upload(int64_t n, int64_t nnz, const int64_t *rp, const int64
         return fail(e == hipErrorOutOfMemory ? SCOCG_ENOMEM : SCOCG_EHIP,
                     std::string("csr_upload: ") + hipGetErrorString(e));
     }
+    keeper().matrix_up();
     *out = H;
     return SCOCG_OK;
 }
@@ -424,6 +576,7 @@ extern "C" int hubbard_upload(int32_t L, int32_t n_up, int32_t n_dn, double t, d
         return fail(e == hipErrorOutOfMemory ? SCOCG_ENOMEM : SCOCG_EHIP, std::string("hubbard_upload: ") +
                                                                               hipGetErrorString(e));
     }
+    keeper().matrix_up();
     *out = H;
     return SCOCG_OK;
 }
@@ -460,6 +613,7 @@ static void csr_release(scocg_csr *H)
     if (H->refs.fetch_sub(1) == 1) {
         free_dev(H->d);
         delete H;
+        keeper().matrix_down();
     }
 }
 
@@ -548,6 +702,7 @@ struct SolveRequest {
 
 int solve(SolveRequest &rq, hipStream_t st)
 {
+    g_call_stream = st;
     const int64_t K = rq.K, M = rq.M;
     if (M <= 0 || K <= 0) return fail(SCOCG_EINVAL, "n_shift and n_rhs must be positive");
     if (!rq.Hj.empty() && (int64_t)rq.Hj.size() != K) return fail(SCOCG_EINVAL, "one matrix per rhs expected");
@@ -715,9 +870,8 @@ int solve(SolveRequest &rq, hipStream_t st)
         if ((int64_t)h_items.size() >= (1LL << 31)) return fail(SCOCG_EINVAL, "batch too large for its work lists");
     }
 
-    DevBuf bz, bseed, bring, bp, bq, bX, bP, bXproj, bprow, bpi, bpip, bbk, bres, biters, bpst, bact, bnact, bah, bbh,
-        brn, bcoef, bp2, bp1, bcnt, bidx, bsd, bstats, bdesc, bwshift, bwslot, bUproj, bblk;
-    auto A = [&](DevBuf &b, size_t bytes) -> hipError_t { return b.alloc(bytes); };
+    DevBuf bseed, bring, bp, bq, bX, bP, bXproj, bpi, bpip, bbk, bact, bah, bbh, brn, bcoef, bp2, bp1, bUproj, bin, bsmall;
+    auto A = [&](DevBuf &b, size_t bytes) -> hipError_t { return b.work(bytes); };
     hipError_t e = hipSuccess;
 #define ALLOC(buf, bytes)                                                                                  \
     do {                                                                                                   \
@@ -726,17 +880,12 @@ int solve(SolveRequest &rq, hipStream_t st)
             return fail(SCOCG_ENOMEM, std::string("device allocation of ") + std::to_string((size_t)(bytes)) + \
                                           " bytes failed: " + hipGetErrorString(e));                      \
     } while (0)
-    ALLOC(bz, nz * sizeof(double2));
     ALLOC(bseed, K * sizeof(SeedState));
     const int R = 2 * TB + 1;  // ring slots: one block's update overlaps the next block's iterations
     ALLOC(bring, (size_t)R * vec * sizeof(double2));
     ALLOC(bp, 2 * vec * sizeof(double2));
     ALLOC(bq, vec * sizeof(double2));
     ALLOC(bP, (size_t)Mst * ntot * esz);
-    if (Mst < M) {
-        ALLOC(bwshift, (size_t)K * Mst * sizeof(int32_t));
-        ALLOC(bwslot, KM * sizeof(int32_t));
-    }
     if (Mst < M || rq.wproj) ALLOC(bUproj, KM * sizeof(double2));
     DevBuf bshist, bpart3;
     if (rq.wproj) {
@@ -745,20 +894,11 @@ int solve(SolveRequest &rq, hipStream_t st)
     }
     const bool x_is_out = need_full && o.precision == 0 && rq.Xout && !rq.keepX;
     if (need_full && !x_is_out) ALLOC(bX, (size_t)M * ntot * esz);
-    ALLOC(bdesc, K * sizeof(RhsDesc));
-    if (!need_full) {
-        ALLOC(bXproj, KM * sizeof(double2));
-        ALLOC(bprow, K * sizeof(int64_t));
-    }
+    if (!need_full) ALLOC(bXproj, KM * sizeof(double2));
     ALLOC(bpi, KM * sizeof(double2));
     ALLOC(bpip, KM * sizeof(double2));
     ALLOC(bbk, KM * sizeof(double2));
-    ALLOC(bres, KM * sizeof(double));
-    ALLOC(biters, KM * sizeof(int32_t));
-    ALLOC(bpst, KM * sizeof(int32_t));
     ALLOC(bact, KM * sizeof(int32_t));
-    ALLOC(bnact, 2 * KM * sizeof(int32_t));
-    ALLOC(bblk, 2 * (size_t)K * 4 * sizeof(int32_t));
     ALLOC(bah, K * TB * sizeof(double2));
     ALLOC(bbh, K * TB * sizeof(double2));
     ALLOC(brn, K * TB * sizeof(double));
@@ -778,91 +918,94 @@ int solve(SolveRequest &rq, hipStream_t st)
     if (s.expanded) ALLOC(bcoefx, 2 * coefx_bytes);
     ALLOC(bp2, K * s.nblk * sizeof(double2));
     ALLOC(bp1, K * s.nblk * sizeof(double));
-    ALLOC(bcnt, K * sizeof(uint32_t));
-    ALLOC(bsd, K * sizeof(int32_t));
-    ALLOC(bstats, 3 * sizeof(unsigned long long));
-    DevBuf bswlog;
-    ALLOC(bswlog, KM * 2 * sizeof(int32_t));
-    if (rq.unit_idx) ALLOC(bidx, K * sizeof(int64_t));
+    // what the report copies to the host in one piece (residuals, statistics, iterations, statuses,
+    // switch log), then the small arrays that start at zero with it
+    const size_t o_stats = KM * sizeof(double), o_iters = o_stats + 4 * sizeof(unsigned long long);
+    const size_t o_pst = o_iters + KM * sizeof(int32_t), o_swlog = o_pst + KM * sizeof(int32_t);
+    const size_t rep_bytes = o_swlog + 2 * KM * sizeof(int32_t);
+    const size_t o_nact = rep_bytes, o_blk = o_nact + 2 * KM * sizeof(int32_t);
+    const size_t o_cnt = o_blk + 2 * (size_t)K * 4 * sizeof(int32_t), small_bytes = o_cnt + K * sizeof(uint32_t);
+    ALLOC(bsmall, small_bytes);
+    // the call's tables, copied to the device in one piece
+    std::vector<char> h_in;
+    auto put = [&](const void *src, size_t bytes) -> size_t {
+        const size_t at = (h_in.size() + 255) / 256 * 256;
+        h_in.resize(at + bytes);
+        if (bytes) std::memcpy(h_in.data() + at, src, bytes);
+        return at;
+    };
+    std::vector<int64_t> no_row;
+    if (rq.wproj) no_row.assign(K, -1);  // no kept row: every pair's projection is carried by scalars
+    const size_t i_z = put(rq.z, nz * sizeof(double2)), i_desc = put(hdesc.data(), K * sizeof(RhsDesc));
+    const size_t i_sd = put(seeds.data(), K * sizeof(int32_t));
+    const size_t i_idx = rq.unit_idx ? put(rq.unit_idx, K * sizeof(int64_t)) : 0;
+    const size_t i_row = rq.wproj ? put(no_row.data(), K * sizeof(int64_t)) : i_idx;
+    const size_t i_wshift = put(h_wshift.data(), h_wshift.size() * sizeof(int32_t));
+    const size_t i_wslot = put(h_wslot.data(), h_wslot.size() * sizeof(int32_t));
+    const size_t i_items = put(h_items.data(), h_items.size() * sizeof(int2));
+    ALLOC(bin, h_in.size());
+    char *const din = bin.as<char>();
+    char *const dsm = bsmall.as<char>();
+    HIPCHK(hipMemcpyAsync(din, h_in.data(), h_in.size(), hipMemcpyHostToDevice, st));
+    const int64_t *d_idx = rq.unit_idx ? (const int64_t *)(din + i_idx) : nullptr;
 
-    s.z = bz.as<double2>();
+    s.z = (const double2 *)(din + i_z);
     s.seed = bseed.as<SeedState>();
     s.ring = bring.as<double2>();
     s.R = R;
-    s.blk = bblk.as<int32_t>();
+    s.blk = (int32_t *)(dsm + o_blk);
     s.p = bp.as<double2>();
     s.q = bq.as<double2>();
     s.P = bP.ptr;
     s.Mst = Mst;
-    s.wshift = Mst < M ? bwshift.as<int32_t>() : nullptr;
-    s.wslot = Mst < M ? bwslot.as<int32_t>() : nullptr;
+    s.wshift = Mst < M ? (const int32_t *)(din + i_wshift) : nullptr;
+    s.wslot = Mst < M ? (const int32_t *)(din + i_wslot) : nullptr;
     s.Uproj = (Mst < M || rq.wproj) ? bUproj.as<double2>() : nullptr;
     s.wproj = rq.wproj;
     s.shist = rq.wproj ? bshist.as<double2>() : nullptr;
     s.part3 = rq.wproj ? bpart3.as<double2>() : nullptr;
     s.X = need_full ? (x_is_out ? (void *)rq.Xout : bX.ptr) : nullptr;
     s.Xproj = need_full ? nullptr : bXproj.as<double2>();
-    s.proj_row = need_full ? nullptr : bprow.as<int64_t>();
+    s.proj_row = need_full ? nullptr : (const int64_t *)(din + i_row);
     s.pi = bpi.as<double2>();
     s.pi_prev = bpip.as<double2>();
     s.beta_k = bbk.as<double2>();
-    s.res = bres.as<double>();
-    s.iters = biters.as<int32_t>();
-    s.pstatus = bpst.as<int32_t>();
+    s.res = (double *)dsm;
+    s.iters = (int32_t *)(dsm + o_iters);
+    s.pstatus = (int32_t *)(dsm + o_pst);
     s.active = bact.as<int32_t>();
-    s.nact = bnact.as<int32_t>();
+    s.nact = (int32_t *)(dsm + o_nact);
     s.ahist = bah.as<double2>();
     s.bhist = bbh.as<double2>();
     s.rnhist = brn.as<double>();
     s.coef = bcoef.ptr;
     s.part2 = bp2.as<double2>();
     s.part1 = bp1.as<double>();
-    s.cnt = bcnt.as<uint32_t>();
-    s.stats = bstats.as<unsigned long long>();
-    s.swlog = bswlog.as<int32_t>();
-    s.desc = bdesc.as<RhsDesc>();
-    DevBuf bitems;
+    s.cnt = (uint32_t *)(dsm + o_cnt);
+    s.stats = (unsigned long long *)(dsm + o_stats);
+    s.swlog = (int32_t *)(dsm + o_swlog);
+    s.desc = (const RhsDesc *)(din + i_desc);
     if (uneven) {
-        ALLOC(bitems, h_items.size() * sizeof(int2));
-        HIPCHK(hipMemcpyAsync(bitems.ptr, h_items.data(), h_items.size() * sizeof(int2), hipMemcpyHostToDevice, st));
-        s.it_grp = bitems.as<int2>();
+        const int2 *items = (const int2 *)(din + i_items);
+        s.it_grp = items;
         s.n_it_grp = n_grp;
-        s.it_rhs = bitems.as<int2>() + n_grp;
+        s.it_rhs = items + n_grp;
         s.n_it_rhs = n_rhs_items;
-        s.it_upd = bitems.as<int2>() + n_grp + n_rhs_items;
+        s.it_upd = items + n_grp + n_rhs_items;
         s.n_it_upd = n_upd;
     }
 
-    HIPCHK(hipMemcpyAsync(bdesc.ptr, hdesc.data(), K * sizeof(RhsDesc), hipMemcpyHostToDevice, st));
-    if (Mst < M) {
-        HIPCHK(hipMemcpyAsync(bwshift.ptr, h_wshift.data(), h_wshift.size() * sizeof(int32_t), hipMemcpyHostToDevice,
-                              st));
-        HIPCHK(hipMemcpyAsync(bwslot.ptr, h_wslot.data(), h_wslot.size() * sizeof(int32_t), hipMemcpyHostToDevice, st));
-    }
-    HIPCHK(hipMemcpyAsync(bz.ptr, rq.z, nz * sizeof(double2), hipMemcpyHostToDevice, st));
-    HIPCHK(hipMemcpyAsync(bsd.ptr, seeds.data(), K * sizeof(int32_t), hipMemcpyHostToDevice, st));
-    if (rq.unit_idx) {
-        HIPCHK(hipMemcpyAsync(bidx.ptr, rq.unit_idx, K * sizeof(int64_t), hipMemcpyHostToDevice, st));
-        if (!need_full) HIPCHK(hipMemcpyAsync(bprow.ptr, rq.unit_idx, K * sizeof(int64_t), hipMemcpyHostToDevice, st));
-    }
-    std::vector<int64_t> no_row;
-    if (rq.wproj) {
-        // no kept row: every pair's projection is carried by scalars
-        no_row.assign(K, -1);
-        HIPCHK(hipMemcpyAsync(bprow.ptr, no_row.data(), K * sizeof(int64_t), hipMemcpyHostToDevice, st));
-    }
-    HIPCHK(launch_zero(bcnt.ptr, K * sizeof(uint32_t), st));
-    HIPCHK(launch_zero(bnact.ptr, 2 * KM * sizeof(int32_t), st));
-    HIPCHK(launch_zero(bblk.ptr, 2 * (size_t)K * 4 * sizeof(int32_t), st));
-    HIPCHK(launch_zero(bstats.ptr, 3 * sizeof(unsigned long long), st));
-    HIPCHK(launch_zero(bswlog.ptr, KM * 2 * sizeof(int32_t), st));
+    HIPCHK(launch_zero(dsm, small_bytes, st));
     if (need_full) HIPCHK(launch_zero(s.X, (size_t)M * ntot * esz, st));
     HIPCHK(launch_zero(s.p, 2 * vec * sizeof(double2), st));
-    HIPCHK(launch_init(s, rq.B, rq.unit_idx ? bidx.as<int64_t>() : nullptr, bsd.as<int32_t>(), limit, st));
+    HIPCHK(launch_init(s, rq.B, d_idx, (const int32_t *)(din + i_sd), limit, st));
 
     PinnedBuf host_state;
-    HIPCHK(host_state.alloc(2 * K * sizeof(SeedState)));
+    const size_t state_bytes = 2 * K * sizeof(SeedState);
+    std::vector<char> rep_big(rep_bytes > (4ull << 20) ? rep_bytes : 0);  // (not worth pinning)
+    HIPCHK(host_state.alloc(state_bytes + (rep_big.empty() ? rep_bytes : 0)));
     SeedState *hs = (SeedState *)host_state.ptr;
+    char *const h_rep = rep_big.empty() ? (char *)host_state.ptr + state_bytes : rep_big.data();
 
     std::vector<hipEvent_t> evs;
     struct EvList {
@@ -912,8 +1055,8 @@ int solve(SolveRequest &rq, hipStream_t st)
     for (int q = 0; q < 2; ++q) {
         sp[q].coef = (char *)bcoef.ptr + q * coef_bytes;
         sp[q].coefx = s.expanded ? (double *)((char *)bcoefx.ptr + q * coefx_bytes) : nullptr;
-        sp[q].nact = bnact.as<int32_t>() + q * KM;
-        sp[q].blk = bblk.as<int32_t>() + q * (size_t)K * 4;
+        sp[q].nact = s.nact + q * KM;
+        sp[q].blk = s.blk + q * (size_t)K * 4;
     }
     // update-kernel timing: a ring of event pairs on the update stream, read back lazily
     constexpr int NE = 8;
@@ -1049,24 +1192,22 @@ int solve(SolveRequest &rq, hipStream_t st)
             else if (rq.keepX) g.X = rq.keepX->ptr;
             else return fail(SCOCG_EINVAL, "FP32 greens_diag needs projection mode");
         }
-        HIPCHK(launch_gather_diag(g, rq.unit_idx ? bidx.as<int64_t>() : nullptr, rq.Gout, st));
+        HIPCHK(launch_gather_diag(g, d_idx, rq.Gout, st));
     }
     HIPCHK(hipEventRecord(ev_t1, st));
 
     // report
-    std::vector<int32_t> h_it(KM), h_st(KM);
-    std::vector<double> h_res(KM), h_true(KM, -1.0);
-    HIPCHK(hipMemcpyAsync(h_it.data(), s.iters, KM * sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    HIPCHK(hipMemcpyAsync(h_st.data(), s.pstatus, KM * sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    HIPCHK(hipMemcpyAsync(h_res.data(), s.res, KM * sizeof(double), hipMemcpyDeviceToHost, st));
-    unsigned long long h_stats[3] = {0, 0, 0};
-    HIPCHK(hipMemcpyAsync(h_stats, s.stats, sizeof(h_stats), hipMemcpyDeviceToHost, st));
+    std::vector<double> h_true(KM, -1.0);
+    HIPCHK(hipMemcpyAsync(h_rep, dsm, rep_bytes, hipMemcpyDeviceToHost, st));
+    HIPCHK(hipStreamSynchronize(st));
+    const double *h_res = (const double *)h_rep;
+    const unsigned long long *h_stats = (const unsigned long long *)(h_rep + o_stats);
+    const int32_t *h_it = (const int32_t *)(h_rep + o_iters), *h_st = (const int32_t *)(h_rep + o_pst);
+    const int32_t *h_sw = (const int32_t *)(h_rep + o_swlog);
     g_swlog.K = K;
     g_swlog.M = M;
     g_swlog.count.resize(K);
-    g_swlog.log.resize(KM * 2);
-    HIPCHK(hipMemcpyAsync(g_swlog.log.data(), s.swlog, KM * 2 * sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    HIPCHK(hipStreamSynchronize(st));
+    g_swlog.log.assign(h_sw, h_sw + KM * 2);
     for (int64_t j = 0; j < K; ++j) g_swlog.count[j] = hs[j].switches;
     g_timing.update_bytes = (double)h_stats[0];
     g_timing.update_flops = (double)h_stats[2];
@@ -1090,7 +1231,7 @@ int solve(SolveRequest &rq, hipStream_t st)
         const scocg_timing saved = g_timing;
         const SwitchLog saved_log = g_swlog;
         const int64_t gx = s.nblk;
-        const int64_t *uidx = rq.unit_idx ? bidx.as<int64_t>() : nullptr;
+        const int64_t *uidx = d_idx;
         std::vector<double> h_nb(K);
         for (int64_t j = 0; j < K; ++j) h_nb[j] = hs[j].nb;
         DevBuf bnb, part, outr;
@@ -1240,13 +1381,14 @@ extern "C" int krylov_greens_diag(scocg_csr_t H, int64_t n_shift, const double *
     for (int64_t k = 0; k < 2 * n_shift; ++k)
         if (!std::isfinite(z[k])) return fail(SCOCG_EINVAL, "non-finite shift");
     hipStream_t st = (hipStream_t)stream;
+    g_call_stream = st;
     g_timing = scocg_timing{};
     const int64_t Kp = (n_rhs + LZ_RB - 1) / LZ_RB * LZ_RB;  // padded with finished entries
     const int64_t nblk = (n + LZ_TILE - 1) / LZ_TILE;
     DevBuf bV0, bV1, bW0, bW1, bpart, bab, bst, bz;
     hipError_t e = hipSuccess;
     auto A = [&](DevBuf &b, size_t bytes) {
-        if (e == hipSuccess) e = b.alloc(bytes);
+        if (e == hipSuccess) e = b.work(bytes);
     };
     const size_t vbytes = (size_t)Kp * n * sizeof(double);
     A(bV0, vbytes);
@@ -1325,13 +1467,14 @@ extern "C" int krylov_greens_vec(scocg_csr_t H, int64_t n_shift, const double *z
     for (int64_t k = 0; k < 2 * n_shift; ++k)
         if (!std::isfinite(z[k])) return fail(SCOCG_EINVAL, "non-finite shift");
     hipStream_t st = (hipStream_t)stream;
+    g_call_stream = st;
     g_timing = scocg_timing{};
     const int64_t n = H->d.n;
     const int64_t nblk = (n + LZ_TILE - 1) / LZ_TILE;
     DevBuf bxs, bV0, bV1, bW0, bW1, bpart, bab, bst, bz, bscal;
     hipError_t e = hipSuccess;
     auto A = [&](DevBuf &buf, size_t bytes) {
-        if (e == hipSuccess) e = buf.alloc(bytes);
+        if (e == hipSuccess) e = buf.work(bytes);
     };
     A(bxs, n * sizeof(double));
     for (DevBuf *v : {&bV0, &bV1, &bW0, &bW1}) A(*v, (size_t)n * sizeof(double));
@@ -1409,12 +1552,13 @@ extern "C" int ground_state(scocg_csr_t H, const double *x0, int32_t nu, double 
     if (nu < 2 || nu > (1 << 20)) return fail(SCOCG_EINVAL, "nu must be in [2, 2^20]");
     if (!(tol > 0) || max_sweeps < 0) return fail(SCOCG_EINVAL, "tol must be positive and max_sweeps >= 0");
     hipStream_t st = (hipStream_t)stream;
+    g_call_stream = st;
     const int64_t n = H->d.n;
     const int64_t nblk = (n + LZ_TILE - 1) / LZ_TILE;
     DevBuf bxs, bV0, bV1, bW0, bW1, bpart, bab, bst, beig, bu, bscr, bacc, by, bscal, bzb, bzx;
     hipError_t e = hipSuccess;
     auto A = [&](DevBuf &b, size_t bytes) {
-        if (e == hipSuccess) e = b.alloc(bytes);
+        if (e == hipSuccess) e = b.work(bytes);
     };
     // the recurrence of one plain vector (no interleaved group)
     A(bxs, n * sizeof(double));
@@ -1996,14 +2140,15 @@ extern "C" int density_matrix_energy(scocg_csr_t H, int64_t n_quad, const double
     int64_t maxrow = 0;
     for (int64_t i = 0; i < d.n; ++i) maxrow = std::max<int64_t>(maxrow, H->h_row_ptr[i + 1] - H->h_row_ptr[i]);
     hipStream_t st = (hipStream_t)stream;
+    g_call_stream = st;
     int64_t batch = rhs_batch > 0 ? rhs_batch : std::min<int64_t>(n_rhs, 256);
     batch = std::min(batch, n_rhs);
     const int64_t nchunk = dE_dval ? pair_outer_chunks(d.n, batch * n_quad, (int)maxrow) : 0;
     DevBuf bw, bz, bidx, bX, bEp, bc, bpart;
-    if (bw.alloc(n_quad * sizeof(double2)) || bz.alloc(n_quad * sizeof(double2)) ||
-        bidx.alloc(batch * sizeof(int64_t)) || bX.alloc((size_t)batch * n_quad * d.n * sizeof(double2)) ||
-        bEp.alloc(batch * sizeof(double)) || bc.alloc((size_t)batch * n_quad * sizeof(double2)) ||
-        bpart.alloc((size_t)nchunk * (size_t)d.nnz * sizeof(double)))
+    if (bw.work(n_quad * sizeof(double2)) || bz.work(n_quad * sizeof(double2)) ||
+        bidx.work(batch * sizeof(int64_t)) || bX.work((size_t)batch * n_quad * d.n * sizeof(double2)) ||
+        bEp.work(batch * sizeof(double)) || bc.work((size_t)batch * n_quad * sizeof(double2)) ||
+        bpart.work((size_t)nchunk * (size_t)d.nnz * sizeof(double)))
         return fail(SCOCG_ENOMEM, "density_matrix_energy: device allocation failed");
     HIPCHK(hipMemcpyAsync(bw.ptr, w, n_quad * sizeof(double2), hipMemcpyHostToDevice, st));
     HIPCHK(hipMemcpyAsync(bz.ptr, z, n_quad * sizeof(double2), hipMemcpyHostToDevice, st));
@@ -2050,10 +2195,11 @@ extern "C" int backward(scocg_tape_t tape, const double *grad_G, double *grad_va
     for (int64_t i = 0; i < d.n; ++i)
         maxrow = std::max<int64_t>(maxrow, tape->H->h_row_ptr[i + 1] - tape->H->h_row_ptr[i]);
     hipStream_t st = (hipStream_t)stream;
+    g_call_stream = st;
     const int64_t npairs = tape->K * tape->M;
     const int64_t nchunk = pair_outer_chunks(d.n, npairs, (int)maxrow);
     DevBuf bc, bpart;
-    if (bc.alloc((size_t)npairs * sizeof(double2)) || bpart.alloc((size_t)nchunk * (size_t)d.nnz * sizeof(double)))
+    if (bc.work((size_t)npairs * sizeof(double2)) || bpart.work((size_t)nchunk * (size_t)d.nnz * sizeof(double)))
         return fail(SCOCG_ENOMEM, "backward: allocation failed");
     HIPCHK(launch_pair_weights(1, tape->K, tape->M, nullptr, nullptr, (const double2 *)grad_G, bc.as<double2>(), st));
     HIPCHK(launch_pair_outer(d.n, npairs, tape->X.as<double2>(), bc.as<double2>(), d.d_row_ptr, d.d_col, d.nnz,
