@@ -543,7 +543,13 @@ extern "C" int hubbard_upload(int32_t L, int32_t n_up, int32_t n_dn, double t, d
     auto bytes4 = [](size_t c) { return ((c * 4 + 255) / 256) * 256; };
     const size_t o_uptr = 0, o_uhop = o_uptr + bytes4(up.ptr.size()), o_ucf = o_uhop + bytes4(up.hop.size());
     const size_t o_dptr = o_ucf + bytes4(up.conf.size()), o_dhop = o_dptr + bytes4(dn.ptr.size());
-    const size_t o_dcf = o_dhop + bytes4(dn.hop.size()), total = o_dcf + bytes4(dn.conf.size());
+    const size_t o_dcf = o_dhop + bytes4(dn.hop.size());
+    int dn_slots = 0;
+    for (int64_t b = 0; b < Dd; ++b) dn_slots = std::max<int>(dn_slots, dn.ptr[b + 1] - dn.ptr[b]);
+    std::vector<uint32_t> slot((size_t)dn_slots * Dd, ~0u);
+    for (int64_t b = 0; b < Dd; ++b)
+        for (int32_t m = dn.ptr[b]; m < dn.ptr[b + 1]; ++m) slot[(size_t)(m - dn.ptr[b]) * Dd + b] = dn.hop[m];
+    const size_t o_dsl = o_dcf + bytes4(dn.conf.size()), total = o_dsl + bytes4(slot.size());
     std::vector<char> blob(total, 0);
     std::memcpy(blob.data() + o_uptr, up.ptr.data(), up.ptr.size() * 4);
     std::memcpy(blob.data() + o_uhop, up.hop.data(), up.hop.size() * 4);
@@ -551,6 +557,7 @@ extern "C" int hubbard_upload(int32_t L, int32_t n_up, int32_t n_dn, double t, d
     std::memcpy(blob.data() + o_dptr, dn.ptr.data(), dn.ptr.size() * 4);
     std::memcpy(blob.data() + o_dhop, dn.hop.data(), dn.hop.size() * 4);
     std::memcpy(blob.data() + o_dcf, dn.conf.data(), dn.conf.size() * 4);
+    if (!slot.empty()) std::memcpy(blob.data() + o_dsl, slot.data(), slot.size() * 4);
     char *dev = nullptr;
     hipError_t e = upload(&dev, blob.data(), blob.size(), st);
     d.d_hub_tables = dev;
@@ -562,6 +569,8 @@ extern "C" int hubbard_upload(int32_t L, int32_t n_up, int32_t n_dn, double t, d
         h.dn_ptr = (const int32_t *)(dev + o_dptr);
         h.dn_hop = (const uint32_t *)(dev + o_dhop);
         h.dn_conf = (const uint32_t *)(dev + o_dcf);
+        h.dn_slot = (const uint32_t *)(dev + o_dsl);
+        h.dn_slots = dn_slots;
         h.Dd = Dd;
         d.hub_Dd = Dd;
         h.t = t;
@@ -826,6 +835,7 @@ int solve(SolveRequest &rq, hipStream_t st)
         // 256 rows; the seed reductions read no more)
         if (dj.hub_Dd > HUB_LDS_MAX || dj.n / dj.hub_Dd > (dj.n + 255) / 256) s.hub_lds = 0;
         s.hub_du_max = std::max<int64_t>(s.hub_du_max, dj.n / dj.hub_Dd);
+        s.hub_dd_max = std::max<int64_t>(s.hub_dd_max, dj.hub_Dd);
     }
     // Work lists for a batch of right-hand sides with different row counts: each per-iteration
     // launch (p update, SpMV, residual update) and the deferred update then covers exactly the
@@ -1954,6 +1964,7 @@ extern "C" int greens_diag_noalloc(scocg_csr_t H, int64_t n_shift, const double 
     if (d.d_hub) {
         if (d.hub_Dd > HUB_LDS_MAX || n / d.hub_Dd > (n + 255) / 256) s.hub_lds = 0;
         s.hub_du_max = n / d.hub_Dd;
+        s.hub_dd_max = d.hub_Dd;
     }
     s.z = L.z;
     s.seed = L.seed;

@@ -120,6 +120,16 @@ __device__ inline int64_t p_index(const SolveDev &s, int64_t j, const RhsDesc &d
     return d.voff + row;
 }
 
+// A pointer that is the same in every lane, in scalar registers.
+template <typename T>
+__device__ inline T *first_lane(T *p)
+{
+    const unsigned long long v = (unsigned long long)p;
+    const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)v);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(v >> 32));
+    return (T *)(((unsigned long long)hi << 32) | lo);
+}
+
 // Matrix arrays reached through a descriptor are global memory; saying so lets the compiler
 // use global (not flat) loads, which wait on the vector-memory counter only.
 template <typename T>

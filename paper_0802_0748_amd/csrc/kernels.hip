@@ -540,98 +540,123 @@ __device__ inline void hubbard_row(const HubbardOp *hp, int64_t row, const doubl
 // stretches p[a, :].  Each row adds its terms in the stored matrix's column order (q equals
 // the stored product bit for bit); the workgroup's partial of p.q goes to slot iu, and the
 // slots past the last configuration are cleared.
-static constexpr int HUB_WG = 1024;
-
-__global__ void __launch_bounds__(HUB_WG) k_spmv_hub_lds(SolveDev s)
+//
+// Bound by the gathers of the up-spin neighbours' blocks (each block is read once per hop, from L2
+// and the Infinity Cache).  RPT rows per thread, HC hops at a time: HC RPT gathers of 16 bytes are
+// in flight per thread whatever the block's size (one hop at a time left a block of at most 1024
+// rows with a single gather in flight), the down-spin hops come slot by slot, the lanes' entries
+// side by side, and the operator's fields are wave-uniform (without first_lane they fill 30 vector
+// registers, and one workgroup fits where two do).  Per product: 924-row blocks (12 sites, 6 + 6,
+// 853,776 rows) 47 -> 25 us, 462-row blocks (11 sites, 5 + 5) 21 -> 10.5 us; 3432-row blocks (14 sites,
+// 7 + 7, 11.8 million rows) stay at 294 us, 1.3 GB of gathers at 4.4 TB/s.
+// (eight waves per SIMD: 64 registers, two workgroups of 1024 threads per compute unit)
+template <int NT, int RPT>
+__global__ void __launch_bounds__(NT, 8) k_spmv_hub_lds(SolveDev s)
 {
-    __shared__ double2 pl[HUB_LDS_MAX];
-    __shared__ double2 sh2[HUB_WG];
+    constexpr int HC = RPT == 1 ? 8 : (RPT == 2 ? 4 : 2);  // up-spin hops gathered at once
+    constexpr int SC = 8;                                  // down-spin hops read at once
+    __shared__ double2 pl[NT * RPT];
+    __shared__ double2 sh2[NT];
     const int64_t j = blockIdx.y;
     const SeedState st = s.seed[j];
     if (!seed_running(st, s.TB)) return;
     const RhsDesc d = s.desc[j];
     if (!d.hub) return;
-    const HubbardOp h = *d.hub;
-    const int64_t Dd = h.Dd;
+    // the operator is the same for every lane: scalar registers
+    HubbardOp h = *d.hub;
+    h.up_ptr = first_lane(h.up_ptr);
+    h.up_hop = first_lane(h.up_hop);
+    h.dn_conf = first_lane(h.dn_conf);
+    h.dn_slot = first_lane(h.dn_slot);
+    h.t = first_lane(h.t);
+    h.U = first_lane(h.U);
+    h.V = first_lane(h.V);
+    h.L = __builtin_amdgcn_readfirstlane(h.L);
+    const int Dd = __builtin_amdgcn_readfirstlane((int)h.Dd);
     const int64_t Du = d.n / Dd;
     const int64_t iu = blockIdx.x;
-    if (iu >= Du) return;
+    if (iu >= Du || Dd > NT * RPT) return;  // (every operator fits: see hub_lds)
     // p of this rhs at row c is pv[RB * c] (RB = 2: interleaved with its partner)
     const int RB = s.spmv_rb;
-    const double2 *pv = s.p + p_index(s, j, d, 0);
+    const double2 *pv = first_lane(s.p + p_index(s, j, d, 0));
     const int64_t r0 = iu * Dd;
-    for (int64_t c = threadIdx.x; c < Dd; c += HUB_WG) pl[c] = pv[(int64_t)RB * (r0 + c)];
-    __syncthreads();
-    const auto *up_ptr = gptr(h.up_ptr);
-    const auto *up_hop = gptr(h.up_hop);
-    const auto *dn_ptr = gptr(h.dn_ptr);
-    const auto *dn_hop = gptr(h.dn_hop);
-    const int32_t u0 = up_ptr[iu], u1 = up_ptr[iu + 1];
-    // up-spin hops to lower configurations come first in the sorted list
-    int32_t usplit = u0;
-    while (usplit < u1 && (int64_t)(up_hop[usplit] & 0x7fffffffu) < iu) ++usplit;
-    const uint32_t cu = gptr(h.up_conf)[iu];
-    auto hop_val = [&](uint32_t e) { return (e >> 31) ? h.t : -h.t; };
-    // Rows of this thread: id = threadIdx.x + i * HUB_WG.  The loops over hops run outside the
-    // loop over rows, so the independent loads of a thread's rows are in flight together;
-    // each row's own sum still takes its terms in column order.
-    constexpr int RPT = (int)((HUB_LDS_MAX + HUB_WG - 1) / HUB_WG);
+    // Rows of this thread: id = threadIdx.x + i * NT (rows past the block repeat its last one,
+    // unused).
+    unsigned id[RPT];
     double ax[RPT], ay[RPT];
 #pragma unroll
     for (int i = 0; i < RPT; ++i) {
+        id[i] = threadIdx.x + i * NT < Dd ? threadIdx.x + i * NT : Dd - 1;
+        pl[id[i]] = pv[(int64_t)RB * r0 + (unsigned)RB * id[i]];
         ax[i] = 0;
         ay[i] = 0;
     }
+    const auto *up_ptr = gptr(h.up_ptr);
+    const auto *up_hop = gptr(h.up_hop);
+    const int32_t u0 = __builtin_amdgcn_readfirstlane(up_ptr[iu]), u1 = __builtin_amdgcn_readfirstlane(up_ptr[iu + 1]);
+    // up-spin hops to lower configurations come first in the sorted list
+    int32_t usplit = u0;
+    while (usplit < u1 && (int64_t)((uint32_t)__builtin_amdgcn_readfirstlane((int)up_hop[usplit]) & 0x7fffffffu) < iu) ++usplit;
+    const uint32_t cu = (uint32_t)__builtin_amdgcn_readfirstlane((int)gptr(h.up_conf)[iu]);
+    auto hop_val = [&](uint32_t e) { return (e >> 31) ? h.t : -h.t; };
     auto up_range = [&](int32_t k0, int32_t k1) {
-        for (int32_t k = k0; k < k1; ++k) {
-            const uint32_t e = up_hop[k];  // the same hop for every row of the block
-            const double v = hop_val(e);
-            const double2 *pa = pv + (int64_t)RB * ((int64_t)(e & 0x7fffffffu) * Dd);
-            double2 pc[RPT];
+        for (int32_t k = k0; k < k1; k += HC) {
+            double v[HC];
+            double2 pc[HC][RPT];
 #pragma unroll
-            for (int i = 0; i < RPT; ++i) {
-                const int64_t id = threadIdx.x + (int64_t)i * HUB_WG;
-                if (id < Dd) pc[i] = pa[(int64_t)RB * id];
+            for (int c = 0; c < HC; ++c) {
+                if (k + c < k1) {
+                    // the same hop for every row of the block
+                    const uint32_t e = (uint32_t)__builtin_amdgcn_readfirstlane((int)up_hop[k + c]);
+                    v[c] = hop_val(e);
+                    const double2 *pa = pv + (int64_t)RB * ((int64_t)(e & 0x7fffffffu) * Dd);
+#pragma unroll
+                    for (int i = 0; i < RPT; ++i) pc[c][i] = pa[(unsigned)RB * id[i]];
+                }
             }
 #pragma unroll
-            for (int i = 0; i < RPT; ++i) {
-                const int64_t id = threadIdx.x + (int64_t)i * HUB_WG;
-                if (id < Dd) {
-                    ax[i] = fma(v, pc[i].x, ax[i]);
-                    ay[i] = fma(v, pc[i].y, ay[i]);
+            for (int c = 0; c < HC; ++c) {
+                if (k + c < k1) {
+#pragma unroll
+                    for (int i = 0; i < RPT; ++i) {
+                        ax[i] = fma(v[c], pc[c][i].x, ax[i]);
+                        ay[i] = fma(v[c], pc[c][i].y, ay[i]);
+                    }
                 }
             }
         }
     };
     up_range(u0, usplit);
-    // the down-spin row of each row from LDS, with the diagonal at its place
+    __syncthreads();
+    // the down-spin row of each row from LDS, with the diagonal at its place (before the first hop
+    // to a higher index)
+    const auto *slot = gptr(h.dn_slot);
+    const int ns = __builtin_amdgcn_readfirstlane(h.dn_slots);
 #pragma unroll
     for (int i = 0; i < RPT; ++i) {
-        const int64_t id = threadIdx.x + (int64_t)i * HUB_WG;
-        if (id >= Dd) continue;
-        const uint32_t cd = gptr(h.dn_conf)[id];
+        const uint32_t cd = gptr(h.dn_conf)[id[i]];
         const int on = __popc(cu & cd);
         const int inter = __popc(cu & ring_next(cu, h.L)) + __popc(cd & ring_next(cd, h.L)) +
                           __popc(cu & ring_next(cd, h.L)) + __popc(cd & ring_next(cu, h.L));
         const double diag = h.U * (double)on + h.V * (double)inter;
-        const double2 pd = pl[id];
+        const double2 pd = pl[id[i]];
         bool diag_done = false;
-        const int32_t d0 = dn_ptr[id], d1 = dn_ptr[id + 1];
-        for (int32_t m0 = d0; m0 < d1; m0 += HUB_CHUNK) {
-            uint32_t e[HUB_CHUNK];
+        for (int m0 = 0; m0 < ns; m0 += SC) {
+            uint32_t e[SC];
 #pragma unroll
-            for (int m = 0; m < HUB_CHUNK; ++m) e[m] = (m0 + m < d1) ? dn_hop[m0 + m] : 0u;
+            for (int c = 0; c < SC; ++c) e[c] = m0 + c < ns ? slot[(unsigned)((m0 + c) * Dd) + id[i]] : ~0u;
 #pragma unroll
-            for (int m = 0; m < HUB_CHUNK; ++m) {
-                if (m0 + m < d1) {
-                    const int64_t b = e[m] & 0x7fffffffu;
-                    if (!diag_done && b > id) {
-                        ax[i] = fma(diag, pd.x, ax[i]);
-                        ay[i] = fma(diag, pd.y, ay[i]);
-                        diag_done = true;
-                    }
+            for (int c = 0; c < SC; ++c) {
+                // (past a configuration's last hop: no column, and the diagonal's turn at the latest)
+                const unsigned b = e[c] & 0x7fffffffu;
+                if (!diag_done && b > id[i]) {
+                    ax[i] = fma(diag, pd.x, ax[i]);
+                    ay[i] = fma(diag, pd.y, ay[i]);
+                    diag_done = true;
+                }
+                if (e[c] != ~0u) {
                     const double2 pc = pl[b];
-                    const double v = hop_val(e[m]);
+                    const double v = hop_val(e[c]);
                     ax[i] = fma(v, pc.x, ax[i]);
                     ay[i] = fma(v, pc.y, ay[i]);
                 }
@@ -641,19 +666,25 @@ __global__ void __launch_bounds__(HUB_WG) k_spmv_hub_lds(SolveDev s)
             ax[i] = fma(diag, pd.x, ax[i]);
             ay[i] = fma(diag, pd.y, ay[i]);
         }
+        if constexpr (RPT > 1) {
+            // one row after the other, not all their loads at once (registers)
+            asm volatile("" : "+v"(ax[i]), "+v"(ay[i])::"memory");
+            __builtin_amdgcn_sched_barrier(0);
+        }
     }
     up_range(usplit, u1);
+    double2 *qg = first_lane(s.q + d.voff + r0);
+    const double2 zs = first_lane(st.zs);
     double2 pq = cmk(0, 0);
 #pragma unroll
     for (int i = 0; i < RPT; ++i) {
-        const int64_t id = threadIdx.x + (int64_t)i * HUB_WG;
-        if (id >= Dd) continue;
-        const double2 pd = pl[id];
-        const double2 qv = cfma(st.zs, pd, make_double2(-ax[i], -ay[i]));
-        s.q[d.voff + r0 + id] = qv;
-        pq = cadd(pq, cmul(pd, qv));
+        if (threadIdx.x + i * NT >= Dd) continue;
+        const double2 pd = pl[id[i]];
+        const double2 qv = cfma(zs, pd, make_double2(-ax[i], -ay[i]));
+        qg[id[i]] = qv;
+        pq = vadd(pq, cmul_f(qv, pd));
     }
-    pq = block_sum2<HUB_WG>(pq, sh2);
+    pq = block_sum2<NT>(pq, sh2);
     if (threadIdx.x == 0) {
         s.part2[j * s.nblk + iu] = pq;
         for (int64_t b = Du + iu; b < s.nblk; b += Du) s.part2[j * s.nblk + b] = cmk(0, 0);
@@ -1714,8 +1745,15 @@ hipError_t launch_seed_iteration(const SolveDev &s, hipStream_t st)
         else hipLaunchKernelGGL((k_spmv<1, false>), dim3((unsigned)nwg), dim3(WG), 0, st, s);
     }
     if (s.has_hub) {
-        if (s.hub_lds)
-            hipLaunchKernelGGL(k_spmv_hub_lds, dim3((unsigned)s.hub_du_max, (unsigned)s.K), dim3(HUB_WG), 0, st, s);
+        if (s.hub_lds) {
+            // by the largest down-spin block; 512 threads give the sums of 1024 (the upper half would
+            // add zeros)
+            const dim3 gh((unsigned)s.hub_du_max, (unsigned)s.K);
+            if (s.hub_dd_max <= 512) hipLaunchKernelGGL((k_spmv_hub_lds<512, 1>), gh, dim3(512), 0, st, s);
+            else if (s.hub_dd_max <= 1024) hipLaunchKernelGGL((k_spmv_hub_lds<1024, 1>), gh, dim3(1024), 0, st, s);
+            else if (s.hub_dd_max <= 2048) hipLaunchKernelGGL((k_spmv_hub_lds<1024, 2>), gh, dim3(1024), 0, st, s);
+            else hipLaunchKernelGGL((k_spmv_hub_lds<1024, 4>), gh, dim3(1024), 0, st, s);
+        }
         else if (RB == 2) hipLaunchKernelGGL((k_spmv<2, true>), dim3((unsigned)nwg), dim3(WG), 0, st, s);
         else hipLaunchKernelGGL((k_spmv<1, true>), dim3((unsigned)nwg), dim3(WG), 0, st, s);
     }

@@ -78,10 +78,12 @@ struct HubbardOp {
     const int32_t *dn_ptr;   // [Dd + 1]
     const uint32_t *dn_hop;
     const uint32_t *dn_conf; // [Dd]
+    const uint32_t *dn_slot; // [dn_slots][Dd] the m-th hop of every down-spin configuration side by side
+                             // (~0 past a configuration's last), so the lanes of a wave read one line
     int64_t Dd;              // down-spin configurations (the fast index of a row)
     double t, U, V;
     int32_t L;               // ring sites
-    int32_t pad;
+    int32_t dn_slots;        // most hops of any down-spin configuration
 };
 
 // Stored matrices of at most SEED_BLOCK_ROWS rows run a block's seed iterations in one launch, one
@@ -197,6 +199,7 @@ struct SolveDev {
     int hub_lds;               // every Hubbard operator's down-spin block fits the LDS-tiled product
     int has_red_small, has_red_big; // some rhs below / at or above 2^21 rows (per-rhs reduction width)
     int64_t hub_du_max;        // largest number of up-spin configurations among them
+    int64_t hub_dd_max;        // largest down-spin block
     unsigned long long *stats; // [0] algorithmic bytes of the deferred update, [1] updated pairs,
                                // [2] its algorithmic flops
     // Work lists of batches whose right-hand sides have different row counts (null otherwise): a
