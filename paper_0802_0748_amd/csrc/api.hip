@@ -544,11 +544,29 @@ extern "C" int hubbard_upload(int32_t L, int32_t n_up, int32_t n_dn, double t, d
     const size_t o_uptr = 0, o_uhop = o_uptr + bytes4(up.ptr.size()), o_ucf = o_uhop + bytes4(up.hop.size());
     const size_t o_dptr = o_ucf + bytes4(up.conf.size()), o_dhop = o_dptr + bytes4(dn.ptr.size());
     const size_t o_dcf = o_dhop + bytes4(dn.hop.size());
-    int dn_slots = 0;
-    for (int64_t b = 0; b < Dd; ++b) dn_slots = std::max<int>(dn_slots, dn.ptr[b + 1] - dn.ptr[b]);
-    std::vector<uint32_t> slot((size_t)dn_slots * Dd, ~0u);
-    for (int64_t b = 0; b < Dd; ++b)
-        for (int32_t m = dn.ptr[b]; m < dn.ptr[b + 1]; ++m) slot[(size_t)(m - dn.ptr[b]) * Dd + b] = dn.hop[m];
+    // the down-spin rows side by side (see HubbardOp::dn_slot; only blocks of up to HUB_LDS_MAX
+    // configurations are read this way)
+    int dn_low = 0, dn_high = 0;
+    std::vector<uint32_t> slot;
+    if (Dd <= HUB_LDS_MAX) {
+        auto low_hops = [&](int64_t b) {
+            int c = 0;
+            for (int32_t m = dn.ptr[b]; m < dn.ptr[b + 1]; ++m) c += (int64_t)(dn.hop[m] & 0x7fffffffu) < b;
+            return c;
+        };
+        for (int64_t b = 0; b < Dd; ++b) {
+            const int lo = low_hops(b);
+            dn_low = std::max(dn_low, lo);
+            dn_high = std::max(dn_high, dn.ptr[b + 1] - dn.ptr[b] - lo);
+        }
+        const uint32_t filler = (uint32_t)Dd | (t < 0 ? 0x80000000u : 0u);
+        slot.assign((size_t)(dn_low + dn_high) * Dd, filler);
+        for (int64_t b = 0; b < Dd; ++b) {
+            const int first = dn_low - low_hops(b);
+            for (int32_t m = dn.ptr[b]; m < dn.ptr[b + 1]; ++m)
+                slot[(size_t)(first + m - dn.ptr[b]) * Dd + b] = dn.hop[m];
+        }
+    }
     const size_t o_dsl = o_dcf + bytes4(dn.conf.size()), total = o_dsl + bytes4(slot.size());
     std::vector<char> blob(total, 0);
     std::memcpy(blob.data() + o_uptr, up.ptr.data(), up.ptr.size() * 4);
@@ -570,7 +588,8 @@ extern "C" int hubbard_upload(int32_t L, int32_t n_up, int32_t n_dn, double t, d
         h.dn_hop = (const uint32_t *)(dev + o_dhop);
         h.dn_conf = (const uint32_t *)(dev + o_dcf);
         h.dn_slot = (const uint32_t *)(dev + o_dsl);
-        h.dn_slots = dn_slots;
+        h.dn_low = dn_low;
+        h.dn_high = dn_high;
         h.Dd = Dd;
         d.hub_Dd = Dd;
         h.t = t;
@@ -1493,6 +1512,10 @@ extern "C" int krylov_greens_vec(scocg_csr_t H, int64_t n_shift, const double *z
     A(bst, sizeof(LzRhs));
     A(bz, (size_t)n_shift * sizeof(double2));
     A(bscal, 8 * sizeof(double));
+    // a matrix-free operator with blocks of the tiled product's sizes
+    const bool tiled = H->d.d_hub && lz_hub_fits(H->d.hub_Dd);
+    DevBuf bedge;
+    if (tiled) A(bedge, (size_t)(n / H->d.hub_Dd) * LZ_TILE * sizeof(double));
     if (e != hipSuccess) return fail(SCOCG_ENOMEM, std::string("device allocation failed: ") + hipGetErrorString(e));
     SvDev v{};
     v.hub = H->d.d_hub;
@@ -1534,6 +1557,9 @@ extern "C" int krylov_greens_vec(scocg_csr_t H, int64_t n_shift, const double *z
     s.ab = ab ? ab : bab.as<double>();
     s.st = bst.as<LzRhs>();
     s.x0 = xs;
+    s.edge = tiled ? bedge.as<double>() : nullptr;
+    s.hub_Dd = H->d.hub_Dd;
+    s.hub_Du = tiled ? n / H->d.hub_Dd : 0;
     s.gscale = nb2;
     TimerEvents evs;
     HIPCHK(evs.create());
@@ -1584,6 +1610,10 @@ extern "C" int ground_state(scocg_csr_t H, const double *x0, int32_t nu, double 
     A(bscal, 8 * sizeof(double));
     A(bzb, n * sizeof(double2));
     A(bzx, n * sizeof(double2));
+    // a matrix-free operator with blocks of the tiled product's sizes
+    const bool tiled = H->d.d_hub && lz_hub_fits(H->d.hub_Dd);
+    DevBuf bedge;
+    if (tiled) A(bedge, (size_t)(n / H->d.hub_Dd) * LZ_TILE * sizeof(double));
     if (e != hipSuccess) return fail(SCOCG_ENOMEM, std::string("device allocation failed: ") + hipGetErrorString(e));
     SvDev v{};
     v.hub = H->d.d_hub;
@@ -1620,6 +1650,9 @@ extern "C" int ground_state(scocg_csr_t H, const double *x0, int32_t nu, double 
     s.ab = bab.as<double>();
     s.st = bst.as<LzRhs>();
     s.x0 = xs;
+    s.edge = tiled ? bedge.as<double>() : nullptr;
+    s.hub_Dd = H->d.hub_Dd;
+    s.hub_Du = tiled ? n / H->d.hub_Dd : 0;
     TimerEvents evs;
     HIPCHK(evs.create());
     hipEvent_t t0 = evs.t0, t1 = evs.t1;

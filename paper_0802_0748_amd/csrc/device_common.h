@@ -120,6 +120,15 @@ __device__ inline int64_t p_index(const SolveDev &s, int64_t j, const RhsDesc &d
     return d.voff + row;
 }
 
+// Up-spin configuration of a workgroup of the tiled Hubbard products.  Workgroups go to the 8 XCDs in
+// turn; each XCD takes a stretch of consecutive configurations, whose hops between low sites lead
+// to configurations a short way off, read by the same L2 (grid: 8 times hub_stretch).
+__host__ __device__ inline int64_t hub_stretch(int64_t Du) { return (Du + 7) / 8; }
+__device__ inline int64_t hub_block(unsigned b, int64_t Du)
+{
+    return (int64_t)(b & 7) * hub_stretch(Du) + (b >> 3);
+}
+
 // A pointer that is the same in every lane, in scalar registers.
 template <typename T>
 __device__ inline T *first_lane(T *p)

@@ -542,20 +542,23 @@ __device__ inline void hubbard_row(const HubbardOp *hp, int64_t row, const doubl
 // slots past the last configuration are cleared.
 //
 // Bound by the gathers of the up-spin neighbours' blocks (each block is read once per hop, from L2
-// and the Infinity Cache).  RPT rows per thread, HC hops at a time: HC RPT gathers of 16 bytes are
+// and the Infinity Cache).  RPT rows per thread, HC hops at a time: 8 to 16 gathers of 16 bytes are
 // in flight per thread whatever the block's size (one hop at a time left a block of at most 1024
 // rows with a single gather in flight), the down-spin hops come slot by slot, the lanes' entries
 // side by side, and the operator's fields are wave-uniform (without first_lane they fill 30 vector
-// registers, and one workgroup fits where two do).  Per product: 924-row blocks (12 sites, 6 + 6,
-// 853,776 rows) 47 -> 25 us, 462-row blocks (11 sites, 5 + 5) 21 -> 10.5 us; 3432-row blocks (14 sites,
-// 7 + 7, 11.8 million rows) stay at 294 us, 1.3 GB of gathers at 4.4 TB/s.
-// (eight waves per SIMD: 64 registers, two workgroups of 1024 threads per compute unit)
+// registers, and one workgroup fits where two do).  The block's up-spin hops are held one per lane
+// and taken with readlane, not read one after the other; down-spin rows are padded with terms of -0,
+// so no lane tests where its hops end.  Per product: 924-row blocks (12 sites, 6 + 6, 853,776 rows)
+// 47 -> 22 us, 462-row blocks (11 sites, 5 + 5) 21 -> 9 us; 3432-row blocks (14 sites, 7 + 7, 11.8
+// million rows) 294 -> 284 us, 1.3 GB of gathers at 4.6 TB/s.
+// (eight waves per SIMD: 64 registers, two workgroups of 1024 threads per compute unit; with four rows
+// per thread 64 registers spill, and one workgroup with twice the gathers in flight does as much)
 template <int NT, int RPT>
-__global__ void __launch_bounds__(NT, 8) k_spmv_hub_lds(SolveDev s)
+__global__ void __launch_bounds__(NT, RPT == 4 ? 4 : 8) k_spmv_hub_lds(SolveDev s)
 {
-    constexpr int HC = RPT == 1 ? 8 : (RPT == 2 ? 4 : 2);  // up-spin hops gathered at once
-    constexpr int SC = 8;                                  // down-spin hops read at once
-    __shared__ double2 pl[NT * RPT];
+    constexpr int HC = RPT == 1 ? 8 : 4;                    // up-spin hops gathered at once
+    constexpr int SC = RPT == 4 ? 4 : 8;                   // down-spin hops read at once
+    __shared__ double2 pl[NT * RPT];  // pl[Dd] = 0 for the fillers
     __shared__ double2 sh2[NT];
     const int64_t j = blockIdx.y;
     const SeedState st = s.seed[j];
@@ -574,8 +577,8 @@ __global__ void __launch_bounds__(NT, 8) k_spmv_hub_lds(SolveDev s)
     h.L = __builtin_amdgcn_readfirstlane(h.L);
     const int Dd = __builtin_amdgcn_readfirstlane((int)h.Dd);
     const int64_t Du = d.n / Dd;
-    const int64_t iu = blockIdx.x;
-    if (iu >= Du || Dd > NT * RPT) return;  // (every operator fits: see hub_lds)
+    const int64_t iu = hub_block(blockIdx.x, Du);
+    if (blockIdx.x >= 8 * hub_stretch(Du) || iu >= Du || Dd >= NT * RPT) return;  // (every operator fits: see hub_lds)
     // p of this rhs at row c is pv[RB * c] (RB = 2: interleaved with its partner)
     const int RB = s.spmv_rb;
     const double2 *pv = first_lane(s.p + p_index(s, j, d, 0));
@@ -591,23 +594,23 @@ __global__ void __launch_bounds__(NT, 8) k_spmv_hub_lds(SolveDev s)
         ax[i] = 0;
         ay[i] = 0;
     }
-    const auto *up_ptr = gptr(h.up_ptr);
-    const auto *up_hop = gptr(h.up_hop);
-    const int32_t u0 = __builtin_amdgcn_readfirstlane(up_ptr[iu]), u1 = __builtin_amdgcn_readfirstlane(up_ptr[iu + 1]);
-    // up-spin hops to lower configurations come first in the sorted list
-    int32_t usplit = u0;
-    while (usplit < u1 && (int64_t)((uint32_t)__builtin_amdgcn_readfirstlane((int)up_hop[usplit]) & 0x7fffffffu) < iu) ++usplit;
+    // the block's up-spin hops (at most 30), one per lane; those to lower configurations come first
+    const int32_t u0 = __builtin_amdgcn_readfirstlane(gptr(h.up_ptr)[iu]);
+    const int nh = __builtin_amdgcn_readfirstlane(gptr(h.up_ptr)[iu + 1]) - u0;
+    const int hl = (int)(threadIdx.x & 63);
+    const uint32_t my_hop = hl < nh ? gptr(h.up_hop)[u0 + hl] : ~0u;
+    const int usplit = __popcll(__ballot(hl < nh && (int64_t)(my_hop & 0x7fffffffu) < iu));
     const uint32_t cu = (uint32_t)__builtin_amdgcn_readfirstlane((int)gptr(h.up_conf)[iu]);
     auto hop_val = [&](uint32_t e) { return (e >> 31) ? h.t : -h.t; };
-    auto up_range = [&](int32_t k0, int32_t k1) {
-        for (int32_t k = k0; k < k1; k += HC) {
+    auto up_range = [&](int k0, int k1) {
+        for (int k = k0; k < k1; k += HC) {
             double v[HC];
             double2 pc[HC][RPT];
 #pragma unroll
             for (int c = 0; c < HC; ++c) {
                 if (k + c < k1) {
                     // the same hop for every row of the block
-                    const uint32_t e = (uint32_t)__builtin_amdgcn_readfirstlane((int)up_hop[k + c]);
+                    const uint32_t e = (uint32_t)__builtin_amdgcn_readlane((int)my_hop, k + c);
                     v[c] = hop_val(e);
                     const double2 *pa = pv + (int64_t)RB * ((int64_t)(e & 0x7fffffffu) * Dd);
 #pragma unroll
@@ -626,12 +629,19 @@ __global__ void __launch_bounds__(NT, 8) k_spmv_hub_lds(SolveDev s)
             }
         }
     };
-    up_range(u0, usplit);
+    if (threadIdx.x == 0) pl[Dd] = cmk(0, 0);
+    up_range(0, usplit);
     __syncthreads();
-    // the down-spin row of each row from LDS, with the diagonal at its place (before the first hop
-    // to a higher index)
+    // the down-spin row of each row from LDS, with the diagonal at its place
     const auto *slot = gptr(h.dn_slot);
-    const int ns = __builtin_amdgcn_readfirstlane(h.dn_slots);
+    const int nl = __builtin_amdgcn_readfirstlane(h.dn_low), nhi = __builtin_amdgcn_readfirstlane(h.dn_high);
+    // a term's value: -t, or +t where bit 31 is set (the sign alone changes); its column's address in
+    // LDS drops the bit
+    const double mt = -h.t;
+    auto dn_val = [&](uint32_t e) -> double {
+        const unsigned long long m = (unsigned long long)__double_as_longlong(mt);
+        return __longlong_as_double((long long)(m ^ ((unsigned long long)(e & 0x80000000u) << 32)));
+    };
 #pragma unroll
     for (int i = 0; i < RPT; ++i) {
         const uint32_t cd = gptr(h.dn_conf)[id[i]];
@@ -639,40 +649,34 @@ __global__ void __launch_bounds__(NT, 8) k_spmv_hub_lds(SolveDev s)
         const int inter = __popc(cu & ring_next(cu, h.L)) + __popc(cd & ring_next(cd, h.L)) +
                           __popc(cu & ring_next(cd, h.L)) + __popc(cd & ring_next(cu, h.L));
         const double diag = h.U * (double)on + h.V * (double)inter;
-        const double2 pd = pl[id[i]];
-        bool diag_done = false;
-        for (int m0 = 0; m0 < ns; m0 += SC) {
-            uint32_t e[SC];
+        auto dn_range = [&](int m, int m1) {
+            for (; m < m1; m += SC) {
+                uint32_t e[SC];
 #pragma unroll
-            for (int c = 0; c < SC; ++c) e[c] = m0 + c < ns ? slot[(unsigned)((m0 + c) * Dd) + id[i]] : ~0u;
+                for (int c = 0; c < SC; ++c)
+                    if (m + c < m1) e[c] = (slot + (m + c) * Dd)[id[i]];
 #pragma unroll
-            for (int c = 0; c < SC; ++c) {
-                // (past a configuration's last hop: no column, and the diagonal's turn at the latest)
-                const unsigned b = e[c] & 0x7fffffffu;
-                if (!diag_done && b > id[i]) {
-                    ax[i] = fma(diag, pd.x, ax[i]);
-                    ay[i] = fma(diag, pd.y, ay[i]);
-                    diag_done = true;
-                }
-                if (e[c] != ~0u) {
-                    const double2 pc = pl[b];
-                    const double v = hop_val(e[c]);
+                for (int c = 0; c < SC; ++c) {
+                    if (m + c >= m1) break;
+                    const double2 pc = *(const double2 *)((const char *)pl + (e[c] << 4));
+                    const double v = dn_val(e[c]);
                     ax[i] = fma(v, pc.x, ax[i]);
                     ay[i] = fma(v, pc.y, ay[i]);
                 }
             }
-        }
-        if (!diag_done) {
-            ax[i] = fma(diag, pd.x, ax[i]);
-            ay[i] = fma(diag, pd.y, ay[i]);
-        }
+        };
+        dn_range(0, nl);
+        const double2 pd = pl[id[i]];
+        ax[i] = fma(diag, pd.x, ax[i]);
+        ay[i] = fma(diag, pd.y, ay[i]);
+        dn_range(nl, nl + nhi);
         if constexpr (RPT > 1) {
             // one row after the other, not all their loads at once (registers)
             asm volatile("" : "+v"(ax[i]), "+v"(ay[i])::"memory");
             __builtin_amdgcn_sched_barrier(0);
         }
     }
-    up_range(usplit, u1);
+    up_range(usplit, nh);
     double2 *qg = first_lane(s.q + d.voff + r0);
     const double2 zs = first_lane(st.zs);
     double2 pq = cmk(0, 0);
@@ -1748,10 +1752,10 @@ hipError_t launch_seed_iteration(const SolveDev &s, hipStream_t st)
         if (s.hub_lds) {
             // by the largest down-spin block; 512 threads give the sums of 1024 (the upper half would
             // add zeros)
-            const dim3 gh((unsigned)s.hub_du_max, (unsigned)s.K);
-            if (s.hub_dd_max <= 512) hipLaunchKernelGGL((k_spmv_hub_lds<512, 1>), gh, dim3(512), 0, st, s);
-            else if (s.hub_dd_max <= 1024) hipLaunchKernelGGL((k_spmv_hub_lds<1024, 1>), gh, dim3(1024), 0, st, s);
-            else if (s.hub_dd_max <= 2048) hipLaunchKernelGGL((k_spmv_hub_lds<1024, 2>), gh, dim3(1024), 0, st, s);
+            const dim3 gh((unsigned)(8 * hub_stretch(s.hub_du_max)), (unsigned)s.K);
+            if (s.hub_dd_max < 512) hipLaunchKernelGGL((k_spmv_hub_lds<512, 1>), gh, dim3(512), 0, st, s);
+            else if (s.hub_dd_max < 1024) hipLaunchKernelGGL((k_spmv_hub_lds<1024, 1>), gh, dim3(1024), 0, st, s);
+            else if (s.hub_dd_max < 2048) hipLaunchKernelGGL((k_spmv_hub_lds<1024, 2>), gh, dim3(1024), 0, st, s);
             else hipLaunchKernelGGL((k_spmv_hub_lds<1024, 4>), gh, dim3(1024), 0, st, s);
         }
         else if (RB == 2) hipLaunchKernelGGL((k_spmv<2, true>), dim3((unsigned)nwg), dim3(WG), 0, st, s);

@@ -46,8 +46,15 @@ struct LzDev {
     const double *x0;    // start vectors [K][n], unit norm, or null for the unit vectors e_j
     double *acc;         // null, or [K][n]: accumulates sum_n coef[k][n] K_n (Ritz vectors)
     const double *coef;  // [K][nu] with acc
+    double *edge;        // [hub_Du][256] products of the tiles two down-spin blocks share (see
+                         // k_lz_hub), or null: the operator's rows one by one
+    int64_t hub_Dd, hub_Du;
     double gscale;       // G is scaled by this: 1 for unit start vectors, |b|^2 for a start vector b
 };
+
+// Down-spin blocks the tiled product takes (krylov.hip: k_lz_hub): a 256-row tile may touch two
+// blocks at most, and a block with its tiles' ends fits four rows per thread.
+inline bool lz_hub_fits(int64_t Dd) { return Dd >= 256 && Dd <= 4 * 1024 - 255; }
 
 // Single real vector of n rows on the stored matrix or the matrix-free operator; one partial
 // per 256-row tile, summed in fixed order by one workgroup into the device scalars scal[].

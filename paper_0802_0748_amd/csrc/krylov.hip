@@ -55,12 +55,25 @@ __device__ inline double sum_tiles(const double *part, int64_t nblk, double *sh)
 {
     double acc = 0;
     int64_t b = threadIdx.x;
-    for (; b + 7 * WG < nblk; b += 8 * WG) {
+    // TILE_LOADS partials in flight per thread (46,010 tiles of the 14-site ring: with 8 in flight
+    // the sum took 19 us, 23 round trips; now 9), the last ones, where a loop would wait for each, as
+    // well: those past the end are not added.  Up to 256 tiles the plain loop's single load does
+    // (726 steps on a 1,176-row crystal, 95 right-hand sides: 17.5 ms with the masked batch, 16.3 so).
+    constexpr int TILE_LOADS = 32;
+    for (; b + (TILE_LOADS - 1) * WG < nblk; b += TILE_LOADS * WG) {
+        double v[TILE_LOADS];
+#pragma unroll
+        for (int u = 0; u < TILE_LOADS; ++u) v[u] = part[b + u * WG];
+#pragma unroll
+        for (int u = 0; u < TILE_LOADS; ++u) acc += v[u];
+    }
+    for (; nblk > WG && b < nblk; b += 8 * WG) {
         double v[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = part[b + u * WG];
+        for (int u = 0; u < 8; ++u) v[u] = b + u * WG < nblk ? part[b + u * WG] : 0.0;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) acc += v[u];
+        for (int u = 0; u < 8; ++u)
+            if (b + u * WG < nblk) acc += v[u];
     }
     for (; b < nblk; b += WG) acc += part[b];
     const int t = threadIdx.x;
@@ -183,6 +196,189 @@ __global__ void __launch_bounds__(WG) k_lz_matvec(LzDev s, int n)
         for (int b = 0; b < RB; ++b)
             if (run[b]) s.part[(g * RB + b) * s.nblk + blockIdx.x] = dot[b];
     }
+}
+
+// The same step for one plain vector on a matrix-free operator whose down-spin blocks fit in LDS: one
+// workgroup per up-spin configuration iu stages x = K_n of its block in LDS, where the down-spin hops
+// read it; the up-spin hops of iu are the same for the whole block and read contiguous stretches.
+// Rows, their terms' order and the 256-row tiles' sums are those of k_lz_matvec (same bits): a
+// thread's rows are counted from the start of the block's first tile (RPT rows, NT apart), so a tile
+// inside the block is summed here, and of a tile that two blocks share each block leaves its products
+// in `edge` for k_lz_edge.
+// Bound by the gathers of the up-spin neighbours (one read of the vector per hop from L2 and the
+// Infinity Cache).  14-site ring, 7 + 7, 11.8 million rows: 448 us with one row per thread and one term
+// at a time, 224 us here (the hops one per lane, taken with readlane, and the tiles' sums in the same
+// kernel: 284 us before those two).
+// FIRST: step 0, where K_n is the start vector.
+template <int RPT, bool FIRST>
+__global__ void __launch_bounds__(1024, 8) k_lz_hub(LzDev s, int n)
+{
+    constexpr int NT = 1024;
+    constexpr int HC = RPT == 4 ? 3 : 8 / RPT;             // up-spin hops gathered at once
+    constexpr int SC = 8;                                  // down-spin hops read at once
+    __shared__ double xl[NT * RPT + 1];  // xl[Dd] = 0 for the fillers
+    __shared__ double dots[NT * RPT];
+    const LzRhs st = s.st[0];
+    if (st.done) return;
+    const int64_t iu = hub_block(blockIdx.x, s.hub_Du);
+    if (iu >= s.hub_Du) return;
+    HubbardOp h = *s.hub;
+    h.up_ptr = first_lane(h.up_ptr);
+    h.up_hop = first_lane(h.up_hop);
+    h.dn_conf = first_lane(h.dn_conf);
+    h.dn_slot = first_lane(h.dn_slot);
+    h.t = first_lane(h.t);
+    h.U = first_lane(h.U);
+    h.V = first_lane(h.V);
+    h.L = __builtin_amdgcn_readfirstlane(h.L);
+    const int nl = __builtin_amdgcn_readfirstlane(h.dn_low), nhi = __builtin_amdgcn_readfirstlane(h.dn_high);
+    // a term's value: -t, or +t where bit 31 is set (the sign alone changes); its column's address in
+    // LDS drops the bit
+    const double mt = -h.t;
+    auto dn_val = [&](uint32_t e) -> double {
+        const unsigned long long m = (unsigned long long)__double_as_longlong(mt);
+        return __longlong_as_double((long long)(m ^ ((unsigned long long)(e & 0x80000000u) << 32)));
+    };
+    const int Dd = (int)s.hub_Dd;
+    const int64_t r0 = iu * Dd;
+    const int off = (int)(r0 & (LZ_TILE - 1));  // rows of the first tile before the block
+    const double bprev = first_lane(st.bprev);
+    const double rb = FIRST ? 1.0 : 1.0 / bprev;
+    const int q = n & 1;
+    const double *Wp = FIRST ? s.x0 : s.W[q ^ 1];
+    const double *Vp = s.V[q ^ 1] + r0;
+    double *Vn = s.V[q] + r0;
+    double *Wn = s.W[q] + r0;
+    // x at `at` rows from row c0 on (wave-uniform c0)
+    auto x_of = [&](int64_t c0, unsigned at) -> double { return FIRST ? (Wp + c0)[at] : (Wp + c0)[at] * rb; };
+    unsigned id[RPT];
+    bool ok[RPT];
+    double acc[RPT];
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) {
+        const int k = (int)threadIdx.x + i * NT - off;
+        ok[i] = k >= 0 && k < Dd;
+        id[i] = (unsigned)min(max(k, 0), Dd - 1);
+        acc[i] = 0.0;
+        if (ok[i]) xl[id[i]] = x_of(r0, id[i]);
+    }
+    // the block's up-spin hops (at most 30), one per lane; those to lower configurations come first
+    const int32_t u0 = __builtin_amdgcn_readfirstlane(gptr(h.up_ptr)[iu]);
+    const int nh = __builtin_amdgcn_readfirstlane(gptr(h.up_ptr)[iu + 1]) - u0;
+    const int hl = (int)(threadIdx.x & 63);
+    const uint32_t my_hop = hl < nh ? gptr(h.up_hop)[u0 + hl] : ~0u;
+    auto hop = [&](int k) -> uint32_t { return (uint32_t)__builtin_amdgcn_readlane((int)my_hop, k); };
+    const int usplit = __popcll(__ballot(hl < nh && (int64_t)(my_hop & 0x7fffffffu) < iu));
+    const uint32_t cu = (uint32_t)__builtin_amdgcn_readfirstlane((int)gptr(h.up_conf)[iu]);
+    auto hop_val = [&](uint32_t e) { return (e >> 31) ? h.t : -h.t; };
+    auto up_range = [&](int k0, int k1) {
+        for (int k = k0; k < k1; k += HC) {
+            double v[HC], x[HC][RPT];
+#pragma unroll
+            for (int c = 0; c < HC; ++c) {
+                if (k + c < k1) {
+                    const uint32_t e = hop(k + c);
+                    v[c] = hop_val(e);
+#pragma unroll
+                    for (int i = 0; i < RPT; ++i) x[c][i] = x_of((int64_t)(e & 0x7fffffffu) * Dd, id[i]);
+                }
+            }
+#pragma unroll
+            for (int c = 0; c < HC; ++c) {
+                if (k + c < k1) {
+#pragma unroll
+                    for (int i = 0; i < RPT; ++i) acc[i] = fma(v[c], x[c][i], acc[i]);
+                }
+            }
+        }
+    };
+    if (threadIdx.x == 0) xl[Dd] = 0.0;
+    up_range(0, usplit);
+    __syncthreads();
+    const auto *slot = gptr(h.dn_slot);
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) {
+        const uint32_t cd = gptr(h.dn_conf)[id[i]];
+        const int on = __popc(cu & cd);
+        const int inter = __popc(cu & ring_next(cu, h.L)) + __popc(cd & ring_next(cd, h.L)) +
+                          __popc(cu & ring_next(cd, h.L)) + __popc(cd & ring_next(cu, h.L));
+        const double diag = h.U * (double)on + h.V * (double)inter;
+        auto dn_range = [&](int m, int m1) {
+            for (; m < m1; m += SC) {
+                uint32_t e[SC];
+#pragma unroll
+                for (int c = 0; c < SC; ++c)
+                    if (m + c < m1) e[c] = (slot + (m + c) * Dd)[id[i]];
+#pragma unroll
+                for (int c = 0; c < SC; ++c) {
+                    if (m + c >= m1) break;
+                    acc[i] = fma(dn_val(e[c]), *(const double *)((const char *)xl + (e[c] << 3)), acc[i]);
+                }
+            }
+        };
+        dn_range(0, nl);
+        acc[i] = fma(diag, xl[id[i]], acc[i]);
+        dn_range(nl, nl + nhi);
+        if constexpr (RPT > 1) {
+            // one row after the other, not all their loads at once (registers)
+            asm volatile("" : "+v"(acc[i])::"memory");
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    up_range(usplit, nh);
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) {
+        double dot = 0.0;
+        if (ok[i]) {
+            const double vo = xl[id[i]];
+            const double wo = FIRST ? acc[i] : fma(-bprev, Vp[id[i]], acc[i]);
+            Vn[id[i]] = vo;
+            Wn[id[i]] = wo;
+            if (s.acc) {
+                double *a = s.acc + r0 + id[i];
+                *a = fma(s.coef[n], vo, *a);
+            }
+            dot = vo * wo;
+        }
+        dots[threadIdx.x + i * NT] = dot;
+    }
+    __syncthreads();
+    // the block's tiles, one per wave: 0 .. nt - 1 from row r0 - off on
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nt = (off + Dd + LZ_TILE - 1) / LZ_TILE;
+    const bool last = iu == s.hub_Du - 1;
+    for (int t = wave; t < nt; t += NT / 64) {
+        const double *dt = dots + LZ_TILE * t + lane;
+        const double d0 = dt[0], d1 = dt[64], d2 = dt[128], d3 = dt[192];
+        const bool head = t == 0 && off > 0, tail = !last && LZ_TILE * (t + 1) > off + Dd;
+        if (head || tail) {
+            // shared with the block before (after) this one: rows of this block only
+            double *e = s.edge + (head ? iu - 1 : iu) * LZ_TILE;
+            const double d[4] = {d0, d1, d2, d3};
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const int k = LZ_TILE * t + lane + 64 * c - off;
+                if (k >= 0 && k < Dd) e[lane + 64 * c] = d[c];
+            }
+        } else {
+            const double v = lane_tree((d0 + d2) + (d1 + d3));
+            if (lane == 0) s.part[r0 / LZ_TILE + t] = v;
+        }
+    }
+}
+
+// the sums of the tiles that the blocks iu and iu + 1 share, one per wave
+__global__ void __launch_bounds__(WG) k_lz_edge(LzDev s)
+{
+    if (s.st[0].done) return;
+    const int lane = threadIdx.x & 63;
+    const int64_t iu = (int64_t)blockIdx.x * (WG / 64) + (threadIdx.x >> 6);
+    const int64_t end = (iu + 1) * s.hub_Dd;
+    if (iu >= s.hub_Du - 1 || (end & (LZ_TILE - 1)) == 0) return;
+    const double *e = s.edge + iu * LZ_TILE + lane;
+    const double v = lane_tree((e[0] + e[128]) + (e[64] + e[192]));
+    if (lane == 0) s.part[end / LZ_TILE] = v;
 }
 
 // a_n from the partials of K_n . w
@@ -504,7 +700,23 @@ hipError_t launch_lanczos_step(const LzDev &s, int n, hipStream_t st)
     const int64_t groups = s.K / s.rb;
     if (s.nblk > 0x7fffffffLL || groups > 65535 || s.K > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     const dim3 gv((unsigned)s.nblk, (unsigned)groups);
-    if (s.rb == 1) hipLaunchKernelGGL(k_lz_matvec<1>, gv, dim3(WG), 0, st, s, n);
+    if (s.rb == 1 && s.edge) {
+        if (!s.hub || s.K != 1 || !s.x0 || !lz_hub_fits(s.hub_Dd) || s.hub_Dd * s.hub_Du != s.n || s.hub_Du > 0x7ffffff0LL)
+            return hipErrorInvalidValue;
+        const dim3 gh((unsigned)(8 * hub_stretch(s.hub_Du)));
+        const int64_t span = s.hub_Dd + LZ_TILE - 1;  // rows from a block's first tile on, at most
+        const int rpt = span <= 1024 ? 1 : (span <= 2048 ? 2 : 4);
+        if (n == 0) {
+            if (rpt == 1) hipLaunchKernelGGL((k_lz_hub<1, true>), gh, dim3(1024), 0, st, s, n);
+            else if (rpt == 2) hipLaunchKernelGGL((k_lz_hub<2, true>), gh, dim3(1024), 0, st, s, n);
+            else hipLaunchKernelGGL((k_lz_hub<4, true>), gh, dim3(1024), 0, st, s, n);
+        } else {
+            if (rpt == 1) hipLaunchKernelGGL((k_lz_hub<1, false>), gh, dim3(1024), 0, st, s, n);
+            else if (rpt == 2) hipLaunchKernelGGL((k_lz_hub<2, false>), gh, dim3(1024), 0, st, s, n);
+            else hipLaunchKernelGGL((k_lz_hub<4, false>), gh, dim3(1024), 0, st, s, n);
+        }
+        hipLaunchKernelGGL(k_lz_edge, dim3((unsigned)((s.hub_Du + 3) / 4)), dim3(WG), 0, st, s);
+    } else if (s.rb == 1) hipLaunchKernelGGL(k_lz_matvec<1>, gv, dim3(WG), 0, st, s, n);
     else hipLaunchKernelGGL(k_lz_matvec<LZ_RB>, gv, dim3(WG), 0, st, s, n);
     hipLaunchKernelGGL(k_lz_alpha, dim3((unsigned)s.K), dim3(WG), 0, st, s, n);
     if (s.rb == 1) hipLaunchKernelGGL(k_lz_axpy<1>, gv, dim3(WG), 0, st, s, n);

@@ -78,12 +78,17 @@ struct HubbardOp {
     const int32_t *dn_ptr;   // [Dd + 1]
     const uint32_t *dn_hop;
     const uint32_t *dn_conf; // [Dd]
-    const uint32_t *dn_slot; // [dn_slots][Dd] the m-th hop of every down-spin configuration side by side
-                             // (~0 past a configuration's last), so the lanes of a wave read one line
+    const uint32_t *dn_slot; // [dn_low + dn_high][Dd]: the down-spin rows side by side, so the lanes of a
+                             // wave read one line.  The hops to lower configurations end at slot
+                             // dn_low - 1 and those to higher ones start at slot dn_low (the
+                             // diagonal stands between them for every row); the others are fillers:
+                             // column Dd (where the reader keeps a 0) and the sign that makes the
+                             // term -0, so that adding it leaves every sum as it is
     int64_t Dd;              // down-spin configurations (the fast index of a row)
     double t, U, V;
     int32_t L;               // ring sites
-    int32_t dn_slots;        // most hops of any down-spin configuration
+    int32_t dn_low, dn_high; // most hops of any down-spin configuration to lower and higher ones
+    int32_t pad;
 };
 
 // Stored matrices of at most SEED_BLOCK_ROWS rows run a block's seed iterations in one launch, one
@@ -103,9 +108,10 @@ inline bool seed_block_fits(int64_t n, int64_t K)
 // Right-hand sides of at least this many rows sum their seed reductions with 1024 threads.
 static constexpr int64_t RED_BIG_ROWS = 1 << 21;
 
-// Down-spin blocks of at most this many configurations take the LDS-tiled product
-// (one 16-byte element per configuration, 64 KB of LDS).
-static constexpr int64_t HUB_LDS_MAX = 4096;
+// Down-spin blocks of at most this many configurations take the LDS-tiled product (one 16-byte element
+// per configuration and a 0 for the fillers, 64 KB of LDS; a ring of 3 to 30 sites has no block of
+// 4096).
+static constexpr int64_t HUB_LDS_MAX = 4095;
 
 // ---- device-side matrix ----
 struct DevCSR {
