@@ -1414,24 +1414,24 @@ extern "C" int krylov_greens_diag(scocg_csr_t H, int64_t n_shift, const double *
     g_timing = scocg_timing{};
     const int64_t Kp = (n_rhs + LZ_RB - 1) / LZ_RB * LZ_RB;  // padded with finished entries
     const int64_t nblk = (n + LZ_TILE - 1) / LZ_TILE;
-    DevBuf bV0, bV1, bW0, bW1, bpart, bab, bst, bz;
+    DevBuf bW0, bW1, bW2, bpart, bab, bst, bz;
     hipError_t e = hipSuccess;
     auto A = [&](DevBuf &b, size_t bytes) {
         if (e == hipSuccess) e = b.work(bytes);
     };
     const size_t vbytes = (size_t)Kp * n * sizeof(double);
-    A(bV0, vbytes);
-    A(bV1, vbytes);
     A(bW0, vbytes);
     A(bW1, vbytes);
-    A(bpart, (size_t)Kp * nblk * sizeof(double));
+    A(bW2, vbytes);
+    A(bpart, (size_t)2 * Kp * nblk * sizeof(double));
     if (!ab) A(bab, (size_t)Kp * 2 * nu * sizeof(double));
-    A(bst, (size_t)Kp * sizeof(LzRhs));
+    A(bst, (size_t)2 * Kp * sizeof(LzRhs));
     A(bz, (size_t)n_shift * sizeof(double2));
     if (e != hipSuccess) return fail(SCOCG_ENOMEM, std::string("device allocation failed: ") + hipGetErrorString(e));
     std::vector<LzRhs> hst(Kp);
     for (int64_t c = 0; c < Kp; ++c) {
         hst[c] = LzRhs{};
+        hst[c].rb = 1.0;
         hst[c].j = c < n_rhs ? rhs_idx[c] : -1;
         hst[c].done = c < n_rhs ? 0 : 1;
     }
@@ -1449,10 +1449,9 @@ extern "C" int krylov_greens_diag(scocg_csr_t H, int64_t n_shift, const double *
     s.gscale = 1.0;
     s.nblk = nblk;
     s.nu = nu;
-    s.V[0] = bV0.as<double>();
-    s.V[1] = bV1.as<double>();
     s.W[0] = bW0.as<double>();
     s.W[1] = bW1.as<double>();
+    s.W[2] = bW2.as<double>();
     s.part = bpart.as<double>();
     s.ab = ab ? ab : bab.as<double>();
     s.st = bst.as<LzRhs>();
@@ -1500,16 +1499,16 @@ extern "C" int krylov_greens_vec(scocg_csr_t H, int64_t n_shift, const double *z
     g_timing = scocg_timing{};
     const int64_t n = H->d.n;
     const int64_t nblk = (n + LZ_TILE - 1) / LZ_TILE;
-    DevBuf bxs, bV0, bV1, bW0, bW1, bpart, bab, bst, bz, bscal;
+    DevBuf bxs, bW0, bW1, bW2, bpart, bab, bst, bz, bscal;
     hipError_t e = hipSuccess;
     auto A = [&](DevBuf &buf, size_t bytes) {
         if (e == hipSuccess) e = buf.work(bytes);
     };
     A(bxs, n * sizeof(double));
-    for (DevBuf *v : {&bV0, &bV1, &bW0, &bW1}) A(*v, (size_t)n * sizeof(double));
+    for (DevBuf *v : {&bW0, &bW1, &bW2}) A(*v, (size_t)n * sizeof(double));
     A(bpart, (size_t)2 * nblk * sizeof(double));
     if (!ab) A(bab, (size_t)2 * nu * sizeof(double));
-    A(bst, sizeof(LzRhs));
+    A(bst, 2 * sizeof(LzRhs));
     A(bz, (size_t)n_shift * sizeof(double2));
     A(bscal, 8 * sizeof(double));
     // a matrix-free operator with blocks of the tiled product's sizes
@@ -1535,6 +1534,7 @@ extern "C" int krylov_greens_vec(scocg_csr_t H, int64_t n_shift, const double *z
     HIPCHK(hipStreamSynchronize(st));
     if (!(nb2 > 0) || !std::isfinite(nb2)) return fail(SCOCG_EINVAL, "the start vector must be nonzero and finite");
     LzRhs h0{};
+    h0.rb = 1.0;
     h0.j = -1;
     HIPCHK(hipMemcpyAsync(bst.ptr, &h0, sizeof(LzRhs), hipMemcpyHostToDevice, st));
     HIPCHK(hipMemcpyAsync(bz.ptr, z, n_shift * sizeof(double2), hipMemcpyHostToDevice, st));
@@ -1549,10 +1549,9 @@ extern "C" int krylov_greens_vec(scocg_csr_t H, int64_t n_shift, const double *z
     s.rb = 1;
     s.nblk = nblk;
     s.nu = nu;
-    s.V[0] = bV0.as<double>();
-    s.V[1] = bV1.as<double>();
     s.W[0] = bW0.as<double>();
     s.W[1] = bW1.as<double>();
+    s.W[2] = bW2.as<double>();
     s.part = bpart.as<double>();
     s.ab = ab ? ab : bab.as<double>();
     s.st = bst.as<LzRhs>();
@@ -1591,17 +1590,17 @@ extern "C" int ground_state(scocg_csr_t H, const double *x0, int32_t nu, double 
     g_call_stream = st;
     const int64_t n = H->d.n;
     const int64_t nblk = (n + LZ_TILE - 1) / LZ_TILE;
-    DevBuf bxs, bV0, bV1, bW0, bW1, bpart, bab, bst, beig, bu, bscr, bacc, by, bscal, bzb, bzx;
+    DevBuf bxs, bW0, bW1, bW2, bpart, bab, bst, beig, bu, bscr, bacc, by, bscal, bzb, bzx;
     hipError_t e = hipSuccess;
     auto A = [&](DevBuf &b, size_t bytes) {
         if (e == hipSuccess) e = b.work(bytes);
     };
     // the recurrence of one plain vector (no interleaved group)
     A(bxs, n * sizeof(double));
-    for (DevBuf *b : {&bV0, &bV1, &bW0, &bW1}) A(*b, (size_t)n * sizeof(double));
+    for (DevBuf *b : {&bW0, &bW1, &bW2}) A(*b, (size_t)n * sizeof(double));
     A(bpart, (size_t)2 * nblk * sizeof(double));
     A(bab, (size_t)2 * nu * sizeof(double));
-    A(bst, sizeof(LzRhs));
+    A(bst, 2 * sizeof(LzRhs));
     A(beig, 2 * sizeof(double));
     A(bu, (size_t)nu * sizeof(double));
     A(bscr, (size_t)nu * sizeof(double));
@@ -1630,6 +1629,7 @@ extern "C" int ground_state(scocg_csr_t H, const double *x0, int32_t nu, double 
     HIPCHK(sv_normalize(v, xs, nullptr, st));
     std::vector<LzRhs> hst(1);
     hst[0] = LzRhs{};
+    hst[0].rb = 1.0;
     hst[0].j = -1;
     LzDev s{};
     s.hub = v.hub;
@@ -1642,10 +1642,9 @@ extern "C" int ground_state(scocg_csr_t H, const double *x0, int32_t nu, double 
     s.rb = 1;
     s.nblk = nblk;
     s.nu = nu;
-    s.V[0] = bV0.as<double>();
-    s.V[1] = bV1.as<double>();
     s.W[0] = bW0.as<double>();
     s.W[1] = bW1.as<double>();
+    s.W[2] = bW2.as<double>();
     s.part = bpart.as<double>();
     s.ab = bab.as<double>();
     s.st = bst.as<LzRhs>();

@@ -21,6 +21,8 @@ constexpr double LZ_STOP_REL = 1e-12;
 
 struct LzRhs {
     double bprev;  // b_n of the step in progress (0 before the first)
+    double rb;     // 1 / b_n (K_n is the vector of step n - 1 times it; 1 before the first)
+    double rb2;    // 1 / b_{n-1}
     double a;      // a_n of the step in progress
     int64_t j;     // row of the unit start vector
     int32_t m;     // steps completed (dimension of the subspace so far)
@@ -37,15 +39,17 @@ struct LzDev {
     int64_t K;     // right-hand sides (padded to groups of rb with finished entries)
     int64_t nblk;  // 256-row tiles, one partial sum each
     int32_t nu;
-    int32_t rb;    // right-hand sides interleaved per group: LZ_RB, or 1 (plain vectors)
-    double *V[2];  // basis vectors K_n by parity of n: [K / rb][n][rb]
-    double *W[2];  // unnormalized next vectors by parity
-    double *part;  // [K][nblk] partial sums
+    int32_t rb;    // right-hand sides interleaved per group: LZ_RB, or 1 (one plain vector)
+    int32_t groups;  // K / rb (set by launch_lanczos_step)
+    double *W[3];  // unnormalized vectors w of step n at n mod 3: [K / rb][n][rb].  The basis vectors are
+                   // not stored: K_n = w_{n-1} / b_n wherever it is read
+    double *part;  // [2][K][nblk] partial sums of K_n . w and of ||w||^2
     double *ab;    // [K][2][nu]: a_1..a_m, then b_2..b_{m+1}
-    LzRhs *st;     // [K]
-    const double *x0;    // start vectors [K][n], unit norm, or null for the unit vectors e_j
-    double *acc;         // null, or [K][n]: accumulates sum_n coef[k][n] K_n (Ritz vectors)
-    const double *coef;  // [K][nu] with acc
+    LzRhs *st;     // [2][K]: by parity of the step where the steps' sums are folded, else and at the
+                   // end the first one
+    const double *x0;    // rb 1: the start vector [n], unit norm; null for the unit vectors e_j (rb LZ_RB)
+    double *acc;         // rb 1: null, or [n]: accumulates sum_n coef[n] K_n (the Ritz vector)
+    const double *coef;  // [nu] with acc
     double *edge;        // [hub_Du][256] products of the tiles two down-spin blocks share (see
                          // k_lz_hub), or null: the operator's rows one by one
     int64_t hub_Dd, hub_Du;
@@ -55,6 +59,10 @@ struct LzDev {
 // Down-spin blocks the tiled product takes (krylov.hip: k_lz_hub): a 256-row tile may touch two
 // blocks at most, and a block with its tiles' ends fits four rows per thread.
 inline bool lz_hub_fits(int64_t Dd) { return Dd >= 256 && Dd <= 4 * 1024 - 255; }
+
+// The sums of a step are folded into the kernels that need them (krylov.hip: k_lz_matvec, k_lz_axpy)
+// up to this many tiles, which one wave sums with four loads per lane.
+constexpr int64_t LZ_FOLD_TILES = 256;
 
 // Single real vector of n rows on the stored matrix or the matrix-free operator; one partial
 // per 256-row tile, summed in fixed order by one workgroup into the device scalars scal[].

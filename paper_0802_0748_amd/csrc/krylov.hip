@@ -4,9 +4,11 @@
 // the local Green's function is then G_jj(z) = [(z - T)^{-1}]_11, evaluated as the continued
 // fraction of T.  Per step, for every unfinished right-hand side:
 //   w = H K_n - b_n K_{n-1};  a_n = K_n . w;  w <- w - a_n K_n;  b_{n+1} = ||w||;
-//   K_{n+1} = w / b_{n+1}  (applied on the fly by the next step as w * (1 / b_{n+1})).
+//   K_{n+1} = w / b_{n+1}  (applied on the fly by the next steps as w * (1 / b_{n+1})).
 // Start vectors are unit vectors, so every basis vector is real.  Sums are fixed-order
 // (per 256-row tile, then the tiles in index order), so results do not depend on scheduling.
+#include <algorithm>
+
 #include "device_common.h"
 #include "hubbard_rows.h"
 #include "krylov.h"
@@ -30,23 +32,62 @@ template <> struct LzRow<1> {
     typedef LzOne T;
 };
 
-// Tree sums of RB values over the WG threads (result in thread 0).
+// Tree sums of RB values over the WG threads: wave b returns the sum of value b in its lane 0.
 template <int RB>
-__device__ inline void block_sum_rb(double (&v)[RB], double (*sh)[WG])
+__device__ inline double block_sum_rb(const double (&v)[RB], double (*sh)[WG])
 {
     const int t = threadIdx.x;
 #pragma unroll
     for (int b = 0; b < RB; ++b) sh[b][t] = v[b];
     __syncthreads();
-    for (int h = WG / 2; h > 0; h >>= 1) {
-        if (t < h) {
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
+    if (wave >= RB) return 0.0;
+    const double *x = sh[wave] + lane;
+    return lane_tree((x[0] + x[128]) + (x[64] + x[192]));
+}
+
+// The sum that sum_tiles gives of at most LZ_FOLD_TILES partials, by one wave (result in lane 0).
+__device__ inline double sum_few_tiles(const double *part, int nblk, int lane)
+{
+    double v[4];
 #pragma unroll
-            for (int b = 0; b < RB; ++b) sh[b][t] += sh[b][t + h];
-        }
-        __syncthreads();
+    for (int c = 0; c < 4; ++c) v[c] = part[min(lane + 64 * c, nblk - 1)];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) v[c] = lane + 64 * c < nblk ? 0.0 + v[c] : 0.0;
+    return lane_tree((v[0] + v[2]) + (v[1] + v[3]));
+}
+
+// Group and tile of a workgroup.  Workgroups go to the 8 XCDs in turn: a row of the grid
+// (8 LZ_SET nblk workgroups) takes 8 LZ_SET groups, LZ_SET to an XCD, tile by tile, so an XCD's L2 holds their
+// vectors for the gathers and each tile of the matrix is read into it once for LZ_SET groups (256 right-
+// hand sides on 16,384 rows, 3.5 MB of matrix: one group after the other 47.5 us, 2 by 2 45.1, 4 by 4
+// 44.4).  In the last row fewer groups are left: they are dealt out over all XCDs.
+constexpr int LZ_SET = 4;
+__device__ inline void lz_place(const LzDev &s, unsigned x, int64_t &g, int64_t &tile)
+{
+    const int64_t g0 = (int64_t)blockIdx.y * (8 * LZ_SET);
+    if (g0 + 8 * LZ_SET <= s.groups) {
+        g = g0 + x % (8 * LZ_SET);
+        tile = x / (8 * LZ_SET);
+    } else {
+        const unsigned q = x / (unsigned)s.nblk;
+        g = g0 + q;
+        tile = x - q * (unsigned)s.nblk;
     }
-#pragma unroll
-    for (int b = 0; b < RB; ++b) v[b] = sh[b][0];
+}
+
+// the state after b_{n+1} = b ended step n
+__device__ inline LzRhs lz_next(LzRhs st, double b, int n, int nu)
+{
+    st.m = n + 1;
+    if (n == nu - 1 || b <= LZ_STOP_REL * (fabs(st.a) + st.bprev)) {
+        st.done = 1;
+    } else {
+        st.rb2 = st.rb;
+        st.bprev = b;
+        st.rb = 1.0 / b;
+    }
+    return st;
 }
 
 // Fixed-order sum of a right-hand side's tile partials by one workgroup (result in thread 0):
@@ -57,8 +98,7 @@ __device__ inline double sum_tiles(const double *part, int64_t nblk, double *sh)
     int64_t b = threadIdx.x;
     // TILE_LOADS partials in flight per thread (46,010 tiles of the 14-site ring: with 8 in flight
     // the sum took 19 us, 23 round trips; now 9), the last ones, where a loop would wait for each, as
-    // well: those past the end are not added.  Up to 256 tiles the plain loop's single load does
-    // (726 steps on a 1,176-row crystal, 95 right-hand sides: 17.5 ms with the masked batch, 16.3 so).
+    // well: those past the end are not added.  Up to 256 tiles the plain loop's single load does.
     constexpr int TILE_LOADS = 32;
     for (; b + (TILE_LOADS - 1) * WG < nblk; b += TILE_LOADS * WG) {
         double v[TILE_LOADS];
@@ -86,116 +126,152 @@ __device__ inline double sum_tiles(const double *part, int64_t nblk, double *sh)
     return sh[0];
 }
 
-// w = H K_n - b_n K_{n-1} and the partials of K_n . w; K_n (= the previous w times 1/b_n, or
-// the unit vector at step 0) is written out for the step after.
-template <int RB>
-__global__ void __launch_bounds__(WG) k_lz_matvec(LzDev s, int n)
+// w = H K_n - b_n K_{n-1} and the partials of K_n . w, with K_n = w_{n-1} / b_n taken from the vectors of
+// the steps before (or the start vector).  UNIT0: step 0
+// from unit vectors.  FOLD: the end of step n - 1 (see k_lz_beta) is worked out
+// here by every workgroup of the group, wave b for right-hand side b; the first tile's keeps it.
+// Bound by memory: three vectors' traffic (w_{n-1}, w_{n-2}, w) besides the matrix, which serves four
+// right-hand sides.  256 right-hand sides, 16,384 rows, 18 entries a row: 45 us
+// when each gather waited for its own column load; 45 with the loads of three slots together and two
+// vectors less to move but 74 registers, 41.7 with 60 (eight waves per SIMD; 2 or 4 slots 42.9 and 45).
+template <int RB, bool FOLD, bool UNIT0>
+__global__ void __launch_bounds__(WG, 8) k_lz_matvec(LzDev s, int n)
 {
     typedef typename LzRow<RB>::T VR;
     __shared__ double sh[RB][WG];
-    const int64_t g = blockIdx.y;
-    bool run[RB];
-    double bprev[RB], rb[RB];
-    int64_t jj[RB];
+    __shared__ LzRhs sst[RB];
+    int64_t g, tile;
+    lz_place(s, blockIdx.x, g, tile);
+    if (g >= s.groups) return;
+    const int lane = (int)(threadIdx.x & 63), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (FOLD && n > 0) {
+        if (wave < RB) {
+            const int64_t j = g * RB + wave;
+            LzRhs st = s.st[(int64_t)((n + 1) & 1) * s.K + j];
+            double b = 0;
+            if (!st.done) {
+                b = sqrt(sum_few_tiles(s.part + (s.K + j) * s.nblk, (int)s.nblk, lane));
+                if (lane == 0 && tile == 0) s.ab[j * 2 * s.nu + s.nu + n - 1] = b;
+                st = lz_next(st, b, n - 1, s.nu);
+            }
+            if (lane == 0) {
+                sst[wave] = st;
+                if (tile == 0) s.st[(int64_t)(n & 1) * s.K + j] = st;
+            }
+        }
+    } else if (lane == 0 && wave < RB) {
+        sst[wave] = s.st[g * RB + wave];
+    }
+    __syncthreads();
+    double bprev[RB], rb[RB], rb2[RB];
     bool any = false;
 #pragma unroll
     for (int b = 0; b < RB; ++b) {
-        const LzRhs st = s.st[g * RB + b];
-        run[b] = !st.done;
-        bprev[b] = run[b] ? st.bprev : 0.0;
-        rb[b] = (run[b] && n > 0) ? 1.0 / st.bprev : 0.0;
-        jj[b] = st.j;
-        any = any || run[b];
+        const double b0 = first_lane(sst[b].bprev), b1 = first_lane(sst[b].rb), b2 = first_lane(sst[b].rb2);
+        const bool run = __builtin_amdgcn_readfirstlane(sst[b].done) == 0;
+        bprev[b] = run ? b0 : 0.0;
+        rb[b] = run ? b1 : 0.0;
+        rb2[b] = run ? b2 : 0.0;
+        any = any || run;
     }
     if (!any) return;  // uniform over the workgroup
-    const int q = n & 1;
     const int64_t base = g * s.n;
-    const VR *Wp = (const VR *)(s.W[q ^ 1]) + base;
-    const VR *Vp = (const VR *)(s.V[q ^ 1]) + base;
-    VR *Vn = (VR *)(s.V[q]) + base;
-    VR *Wn = (VR *)(s.W[q]) + base;
-    const int64_t row = (int64_t)blockIdx.x * WG + threadIdx.x;
+    // w_{n-1} and w_{n-2}; the start vector stands for w_{-1} with a factor of 1
+    const VR *Wp = (const VR *)(RB == 1 && n == 0 ? s.x0 : s.W[(n + 2) % 3]) + base;
+    const VR *Wq = (const VR *)(RB == 1 && n == 1 ? s.x0 : s.W[(n + 1) % 3]) + base;
+    VR *Wn = (VR *)(s.W[n % 3]) + base;
+    const int64_t row = tile * WG + threadIdx.x;
     double dot[RB] = {};
     if (row < s.n) {
         double acc[RB] = {};
-        // one term of the row: acc += v x[c]
-        auto slot = [&](int64_t c, double v) {
-            double x[RB];
-            if (n == 0 && s.x0) {
+        auto entry = [&](int64_t c, double (&x)[RB]) {
+            if constexpr (UNIT0) {
 #pragma unroll
-                for (int b = 0; b < RB; ++b) x[b] = run[b] ? s.x0[(g * RB + b) * s.n + c] : 0.0;
-            } else if (n == 0) {
-#pragma unroll
-                for (int b = 0; b < RB; ++b) x[b] = (c == jj[b]) ? 1.0 : 0.0;
+                for (int b = 0; b < RB; ++b) x[b] = (c == sst[b].j) ? 1.0 : 0.0;
             } else {
                 const VR wc = Wp[c];
 #pragma unroll
                 for (int b = 0; b < RB; ++b) x[b] = wc[b] * rb[b];
             }
-#pragma unroll
-            for (int b = 0; b < RB; ++b) acc[b] = fma(v, x[b], acc[b]);
         };
         if (s.hub) {
             // the operator's terms in the stored row's column order: the same sums
-            hubbard_row_terms(s.hub, row, slot);
+            hubbard_row_terms(s.hub, row, [&](int64_t c, double v) {
+                double x[RB];
+                entry(c, x);
+#pragma unroll
+                for (int b = 0; b < RB; ++b) acc[b] = fma(v, x[b], acc[b]);
+            });
         } else {
-            const int64_t slice = row >> 6;
-            const int lane = (int)(row & 63);
+            const int64_t slice = tile * (WG / 64) + wave;
             const int64_t off = s.slice_ptr[slice];
             const int w = s.slice_w[slice];
             const int32_t *colp = s.ell_col + off + lane;
             const double *valp = s.ell_val + off + lane;
-            // slots in the stored order; column and value loads of LZ_CHUNK slots are issued
-            // before their gathers
-            constexpr int LZ_CHUNK = 4;
-            int k = 0;
-            for (; k + LZ_CHUNK <= w; k += LZ_CHUNK) {
-                int32_t c[LZ_CHUNK];
-                double v[LZ_CHUNK];
+            // slots in the stored order, LZ_CHUNK at a time: the next chunk's columns and values are
+            // on their way during a chunk's gathers, and the gathers are issued together
+            constexpr int LZ_CHUNK = 3;
+            int32_t c[LZ_CHUNK];
+            double v[LZ_CHUNK];
+            auto fetch = [&](int k) {
 #pragma unroll
                 for (int u = 0; u < LZ_CHUNK; ++u) {
-                    c[u] = colp[(int64_t)(k + u) * 64];
-                    v[u] = valp[(int64_t)(k + u) * 64];
+                    const int64_t at = (int64_t)min(k + u, w - 1) * 64;
+                    c[u] = colp[at];
+                    v[u] = valp[at];
                 }
+            };
+            if (w > 0) fetch(0);
+            for (int k = 0; k < w; k += LZ_CHUNK) {
+                double x[LZ_CHUNK][RB], vc[LZ_CHUNK];
+                const int m = min(w - k, LZ_CHUNK);
 #pragma unroll
-                for (int u = 0; u < LZ_CHUNK; ++u) slot(c[u], v[u]);
+                for (int u = 0; u < LZ_CHUNK; ++u) {
+                    vc[u] = v[u];
+                    entry(c[u], x[u]);
+                }
+                fetch(k + LZ_CHUNK);
+#pragma unroll
+                for (int u = 0; u < LZ_CHUNK; ++u) {
+                    if (u < m) {
+#pragma unroll
+                        for (int b = 0; b < RB; ++b) acc[b] = fma(vc[u], x[u][b], acc[b]);
+                    }
+                }
             }
-            for (; k < w; ++k) slot(colp[(int64_t)k * 64], valp[(int64_t)k * 64]);
         }
         VR vo, wo;
+        if constexpr (UNIT0) {
+#pragma unroll
+            for (int b = 0; b < RB; ++b) vo[b] = (row == sst[b].j) ? 1.0 : 0.0;
+        } else {
+            const VR wr = Wp[row];
+#pragma unroll
+            for (int b = 0; b < RB; ++b) vo[b] = wr[b] * rb[b];
+        }
         if (n == 0) {
 #pragma unroll
-            for (int b = 0; b < RB; ++b) {
-                vo[b] = s.x0 ? (run[b] ? s.x0[(g * RB + b) * s.n + row] : 0.0) : ((row == jj[b]) ? 1.0 : 0.0);
-                wo[b] = acc[b];
-            }
+            for (int b = 0; b < RB; ++b) wo[b] = acc[b];
         } else {
-            const VR wr = Wp[row], vr = Vp[row];
+            VR vr;
+            if (RB > 1 && n == 1) {
 #pragma unroll
-            for (int b = 0; b < RB; ++b) {
-                vo[b] = wr[b] * rb[b];
-                wo[b] = fma(-bprev[b], vr[b], acc[b]);
+                for (int b = 0; b < RB; ++b) vr[b] = (row == sst[b].j) ? 1.0 : 0.0;
+            } else {
+                const VR wq = Wq[row];
+#pragma unroll
+                for (int b = 0; b < RB; ++b) vr[b] = wq[b] * rb2[b];
             }
-        }
-        Vn[row] = vo;
-        Wn[row] = wo;
-        if (s.acc) {
 #pragma unroll
-            for (int b = 0; b < RB; ++b)
-                if (run[b]) {
-                    const int64_t k = g * RB + b;
-                    s.acc[k * s.n + row] = fma(s.coef[k * s.nu + n], vo[b], s.acc[k * s.n + row]);
-                }
+            for (int b = 0; b < RB; ++b) wo[b] = fma(-bprev[b], vr[b], acc[b]);
         }
+        Wn[row] = wo;
+        if (RB == 1 && s.acc) s.acc[row] = fma(s.coef[n], vo[0], s.acc[row]);
 #pragma unroll
         for (int b = 0; b < RB; ++b) dot[b] = vo[b] * wo[b];
     }
-    block_sum_rb<RB>(dot, sh);
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int b = 0; b < RB; ++b)
-            if (run[b]) s.part[(g * RB + b) * s.nblk + blockIdx.x] = dot[b];
-    }
+    const double sum = block_sum_rb<RB>(dot, sh);
+    if (lane == 0 && wave < RB && sst[wave].done == 0) s.part[(g * RB + wave) * s.nblk + tile] = sum;
 }
 
 // The same step for one plain vector on a matrix-free operator whose down-spin blocks fit in LDS: one
@@ -207,10 +283,9 @@ __global__ void __launch_bounds__(WG) k_lz_matvec(LzDev s, int n)
 // in `edge` for k_lz_edge.
 // Bound by the gathers of the up-spin neighbours (one read of the vector per hop from L2 and the
 // Infinity Cache).  14-site ring, 7 + 7, 11.8 million rows: 448 us with one row per thread and one term
-// at a time, 224 us here (the hops one per lane, taken with readlane, and the tiles' sums in the same
-// kernel: 284 us before those two).
-// FIRST: step 0, where K_n is the start vector.
-template <int RPT, bool FIRST>
+// at a time, 192 us here (the hops one per lane, taken with readlane, and the tiles' sums in the same
+// kernel: 284 us before those two; 224 while the basis vectors were also written out).
+template <int RPT>
 __global__ void __launch_bounds__(1024, 8) k_lz_hub(LzDev s, int n)
 {
     constexpr int NT = 1024;
@@ -242,15 +317,13 @@ __global__ void __launch_bounds__(1024, 8) k_lz_hub(LzDev s, int n)
     const int Dd = (int)s.hub_Dd;
     const int64_t r0 = iu * Dd;
     const int off = (int)(r0 & (LZ_TILE - 1));  // rows of the first tile before the block
-    const double bprev = first_lane(st.bprev);
-    const double rb = FIRST ? 1.0 : 1.0 / bprev;
-    const int q = n & 1;
-    const double *Wp = FIRST ? s.x0 : s.W[q ^ 1];
-    const double *Vp = s.V[q ^ 1] + r0;
-    double *Vn = s.V[q] + r0;
-    double *Wn = s.W[q] + r0;
+    // w_{n-1} and w_{n-2}; the start vector stands for w_{-1} with a factor of 1
+    const double bprev = first_lane(st.bprev), rb = first_lane(st.rb), rb2 = first_lane(st.rb2);
+    const double *Wp = n == 0 ? s.x0 : s.W[(n + 2) % 3];
+    const double *Wq = (n <= 1 ? s.x0 : s.W[(n + 1) % 3]) + r0;
+    double *Wn = s.W[n % 3] + r0;
     // x at `at` rows from row c0 on (wave-uniform c0)
-    auto x_of = [&](int64_t c0, unsigned at) -> double { return FIRST ? (Wp + c0)[at] : (Wp + c0)[at] * rb; };
+    auto x_of = [&](int64_t c0, unsigned at) -> double { return (Wp + c0)[at] * rb; };
     unsigned id[RPT];
     bool ok[RPT];
     double acc[RPT];
@@ -331,8 +404,7 @@ __global__ void __launch_bounds__(1024, 8) k_lz_hub(LzDev s, int n)
         double dot = 0.0;
         if (ok[i]) {
             const double vo = xl[id[i]];
-            const double wo = FIRST ? acc[i] : fma(-bprev, Vp[id[i]], acc[i]);
-            Vn[id[i]] = vo;
+            const double wo = n == 0 ? acc[i] : fma(-bprev, Wq[id[i]] * rb2, acc[i]);
             Wn[id[i]] = wo;
             if (s.acc) {
                 double *a = s.acc + r0 + id[i];
@@ -394,32 +466,62 @@ __global__ void __launch_bounds__(WG) k_lz_alpha(LzDev s, int n)
     }
 }
 
-// w <- w - a_n K_n and the partials of ||w||^2
-template <int RB>
+// w <- w - a_n K_n and the partials of ||w||^2.  FOLD: a_n (see k_lz_alpha) from the tiles' sums by every
+// workgroup.  Groups and tiles are taken in the opposite order of k_lz_matvec, so that each kernel
+// starts on what the one before left in the caches.  Bound by memory, two vectors read and one
+// written: 17.5 us for 100 MB at the sizes above (5.7 TB/s).
+template <int RB, bool FOLD>
 __global__ void __launch_bounds__(WG) k_lz_axpy(LzDev s, int n)
 {
     typedef typename LzRow<RB>::T VR;
     __shared__ double sh[RB][WG];
-    const int64_t g = blockIdx.y;
-    bool run[RB];
-    double a[RB];
+    __shared__ LzRhs sst[RB];
+    int64_t g, tile;
+    lz_place(s, blockIdx.x, g, tile);
+    if (g >= s.groups) return;
+    const int lane = (int)(threadIdx.x & 63), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (wave < RB) {
+        const int64_t j = g * RB + wave;
+        LzRhs *st = s.st + (FOLD ? (int64_t)(n & 1) * s.K : 0) + j;
+        if (lane == 0) sst[wave] = *st;
+        if (FOLD) {
+            const double an = sum_few_tiles(s.part + j * s.nblk, (int)s.nblk, lane);
+            if (lane == 0 && !sst[wave].done) {
+                sst[wave].a = an;
+                if (tile == 0) {
+                    st->a = an;
+                    s.ab[j * 2 * s.nu + n] = an;
+                }
+            }
+        }
+    }
+    __syncthreads();
+    double a[RB], rb[RB];
     bool any = false;
 #pragma unroll
     for (int b = 0; b < RB; ++b) {
-        const LzRhs st = s.st[g * RB + b];
-        run[b] = !st.done;
-        a[b] = run[b] ? st.a : 0.0;
-        any = any || run[b];
+        const double a0 = first_lane(sst[b].a), b1 = first_lane(sst[b].rb);
+        const bool run = __builtin_amdgcn_readfirstlane(sst[b].done) == 0;
+        a[b] = run ? a0 : 0.0;
+        rb[b] = run ? b1 : 0.0;
+        any = any || run;
     }
     if (!any) return;
-    const int q = n & 1;
     const int64_t base = g * s.n;
-    const VR *Vn = (const VR *)(s.V[q]) + base;
-    VR *Wn = (VR *)(s.W[q]) + base;
-    const int64_t row = (int64_t)blockIdx.x * WG + threadIdx.x;
+    const VR *Wp = (const VR *)(RB == 1 && n == 0 ? s.x0 : s.W[(n + 2) % 3]) + base;
+    VR *Wn = (VR *)(s.W[n % 3]) + base;
+    const int64_t row = tile * WG + threadIdx.x;
     double nn[RB] = {};
     if (row < s.n) {
-        const VR v = Vn[row];
+        VR v;
+        if (RB > 1 && n == 0) {
+#pragma unroll
+            for (int b = 0; b < RB; ++b) v[b] = (row == sst[b].j) ? 1.0 : 0.0;
+        } else {
+            const VR wp = Wp[row];
+#pragma unroll
+            for (int b = 0; b < RB; ++b) v[b] = wp[b] * rb[b];
+        }
         VR w = Wn[row];
 #pragma unroll
         for (int b = 0; b < RB; ++b) {
@@ -428,28 +530,24 @@ __global__ void __launch_bounds__(WG) k_lz_axpy(LzDev s, int n)
         }
         Wn[row] = w;
     }
-    block_sum_rb<RB>(nn, sh);
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int b = 0; b < RB; ++b)
-            if (run[b]) s.part[(g * RB + b) * s.nblk + blockIdx.x] = nn[b];
-    }
+    const double sum = block_sum_rb<RB>(nn, sh);
+    if (lane == 0 && wave < RB && sst[wave].done == 0) s.part[(s.K + g * RB + wave) * s.nblk + tile] = sum;
 }
 
-// b_{n+1} = ||w||, the end test, and the state for the next step
-__global__ void __launch_bounds__(WG) k_lz_beta(LzDev s, int n)
+// b_{n+1} = ||w||, the end test, and the state for the next step (read from half `from` of st)
+__global__ void __launch_bounds__(WG) k_lz_beta(LzDev s, int n, int from)
 {
     __shared__ double sh[WG];
     const int64_t j = blockIdx.x;
-    const LzRhs st = s.st[j];
-    if (st.done) return;
-    const double b = sqrt(sum_tiles(s.part + j * s.nblk, s.nblk, sh));
-    if (threadIdx.x == 0) {
-        s.ab[j * 2 * s.nu + s.nu + n] = b;
-        LzRhs *w = s.st + j;
-        w->m = n + 1;
-        if (n == s.nu - 1 || b <= LZ_STOP_REL * (fabs(st.a) + st.bprev)) w->done = 1;
-        else w->bprev = b;
+    const LzRhs st = s.st[from * s.K + j];
+    if (!st.done) {
+        const double b = sqrt(sum_tiles(s.part + (s.K + j) * s.nblk, s.nblk, sh));
+        if (threadIdx.x == 0) {
+            s.ab[j * 2 * s.nu + s.nu + n] = b;
+            s.st[j] = lz_next(st, b, n, s.nu);
+        }
+    } else if (from && threadIdx.x == 0) {
+        s.st[j] = st;
     }
 }
 
@@ -694,34 +792,47 @@ __global__ void k_fermion_op(const uint32_t *__restrict__ up, const uint32_t *__
     y[k] = make_double2(sg * x[r].x, sg * x[r].y);
 }
 
-hipError_t launch_lanczos_step(const LzDev &s, int n, hipStream_t st)
+hipError_t launch_lanczos_step(const LzDev &s0, int n, hipStream_t st)
 {
+    LzDev s = s0;
     if (s.rb != 1 && s.rb != LZ_RB) return hipErrorInvalidValue;
     const int64_t groups = s.K / s.rb;
     if (s.nblk > 0x7fffffffLL || groups > 65535 || s.K > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-    const dim3 gv((unsigned)s.nblk, (unsigned)groups);
-    if (s.rb == 1 && s.edge) {
-        if (!s.hub || s.K != 1 || !s.x0 || !lz_hub_fits(s.hub_Dd) || s.hub_Dd * s.hub_Du != s.n || s.hub_Du > 0x7ffffff0LL)
+    if (s.nblk * groups > 0x7fffffffLL || (s.rb == 1) != (s.x0 != nullptr) || (s.rb == 1 && s.K != 1))
+        return hipErrorInvalidValue;
+    s.groups = (int32_t)groups;
+    const dim3 gv((unsigned)(s.nblk * std::min<int64_t>(groups, 8 * LZ_SET)), (unsigned)((groups + 8 * LZ_SET - 1) / (8 * LZ_SET)));
+    // up to LZ_FOLD_TILES tiles the sums are worked out by the kernels that need them: two launches a
+    // step instead of four (256 right-hand sides on 16,384 rows: the
+    // two sums' launches were 10 of 72 us a step; 95 on 1,176 rows: 22.6 -> 15 us a step)
+    if (s.nblk <= LZ_FOLD_TILES && !s.edge) {
+        if (s.rb == 1) {
+            hipLaunchKernelGGL((k_lz_matvec<1, true, false>), gv, dim3(WG), 0, st, s, n);
+            hipLaunchKernelGGL((k_lz_axpy<1, true>), gv, dim3(WG), 0, st, s, n);
+        } else {
+            if (n == 0) hipLaunchKernelGGL((k_lz_matvec<LZ_RB, true, true>), gv, dim3(WG), 0, st, s, n);
+            else hipLaunchKernelGGL((k_lz_matvec<LZ_RB, true, false>), gv, dim3(WG), 0, st, s, n);
+            hipLaunchKernelGGL((k_lz_axpy<LZ_RB, true>), gv, dim3(WG), 0, st, s, n);
+        }
+        if (n == s.nu - 1) hipLaunchKernelGGL(k_lz_beta, dim3((unsigned)s.K), dim3(WG), 0, st, s, n, n & 1);
+        return hipGetLastError();
+    }
+    if (s.edge) {
+        if (!s.hub || s.rb != 1 || !lz_hub_fits(s.hub_Dd) || s.hub_Dd * s.hub_Du != s.n || s.hub_Du > 0x7ffffff0LL)
             return hipErrorInvalidValue;
         const dim3 gh((unsigned)(8 * hub_stretch(s.hub_Du)));
         const int64_t span = s.hub_Dd + LZ_TILE - 1;  // rows from a block's first tile on, at most
-        const int rpt = span <= 1024 ? 1 : (span <= 2048 ? 2 : 4);
-        if (n == 0) {
-            if (rpt == 1) hipLaunchKernelGGL((k_lz_hub<1, true>), gh, dim3(1024), 0, st, s, n);
-            else if (rpt == 2) hipLaunchKernelGGL((k_lz_hub<2, true>), gh, dim3(1024), 0, st, s, n);
-            else hipLaunchKernelGGL((k_lz_hub<4, true>), gh, dim3(1024), 0, st, s, n);
-        } else {
-            if (rpt == 1) hipLaunchKernelGGL((k_lz_hub<1, false>), gh, dim3(1024), 0, st, s, n);
-            else if (rpt == 2) hipLaunchKernelGGL((k_lz_hub<2, false>), gh, dim3(1024), 0, st, s, n);
-            else hipLaunchKernelGGL((k_lz_hub<4, false>), gh, dim3(1024), 0, st, s, n);
-        }
+        if (span <= 1024) hipLaunchKernelGGL(k_lz_hub<1>, gh, dim3(1024), 0, st, s, n);
+        else if (span <= 2048) hipLaunchKernelGGL(k_lz_hub<2>, gh, dim3(1024), 0, st, s, n);
+        else hipLaunchKernelGGL(k_lz_hub<4>, gh, dim3(1024), 0, st, s, n);
         hipLaunchKernelGGL(k_lz_edge, dim3((unsigned)((s.hub_Du + 3) / 4)), dim3(WG), 0, st, s);
-    } else if (s.rb == 1) hipLaunchKernelGGL(k_lz_matvec<1>, gv, dim3(WG), 0, st, s, n);
-    else hipLaunchKernelGGL(k_lz_matvec<LZ_RB>, gv, dim3(WG), 0, st, s, n);
+    } else if (s.rb == 1) hipLaunchKernelGGL((k_lz_matvec<1, false, false>), gv, dim3(WG), 0, st, s, n);
+    else if (n == 0) hipLaunchKernelGGL((k_lz_matvec<LZ_RB, false, true>), gv, dim3(WG), 0, st, s, n);
+    else hipLaunchKernelGGL((k_lz_matvec<LZ_RB, false, false>), gv, dim3(WG), 0, st, s, n);
     hipLaunchKernelGGL(k_lz_alpha, dim3((unsigned)s.K), dim3(WG), 0, st, s, n);
-    if (s.rb == 1) hipLaunchKernelGGL(k_lz_axpy<1>, gv, dim3(WG), 0, st, s, n);
-    else hipLaunchKernelGGL(k_lz_axpy<LZ_RB>, gv, dim3(WG), 0, st, s, n);
-    hipLaunchKernelGGL(k_lz_beta, dim3((unsigned)s.K), dim3(WG), 0, st, s, n);
+    if (s.rb == 1) hipLaunchKernelGGL((k_lz_axpy<1, false>), gv, dim3(WG), 0, st, s, n);
+    else hipLaunchKernelGGL((k_lz_axpy<LZ_RB, false>), gv, dim3(WG), 0, st, s, n);
+    hipLaunchKernelGGL(k_lz_beta, dim3((unsigned)s.K), dim3(WG), 0, st, s, n, 0);
     return hipGetLastError();
 }
 
