@@ -108,6 +108,10 @@ inline bool seed_block_fits(int64_t n, int64_t K)
 // Right-hand sides of at least this many rows sum their seed reductions with 1024 threads.
 static constexpr int64_t RED_BIG_ROWS = 1 << 21;
 
+// Up to this many 256-row tiles (stored matrices) the seed reductions are folded into the kernels that
+// need them, which one wave sums with four loads per lane.
+static constexpr int64_t FOLD_TILES = 256;
+
 // Down-spin blocks of at most this many configurations take the LDS-tiled product (one 16-byte element
 // per configuration and a 0 for the fillers, 64 KB of LDS; a ring of 3 to 30 sites has no block of
 // 4096).
@@ -237,8 +241,6 @@ hipError_t launch_pack_report(int64_t K, int64_t M, int fixed, const int32_t *it
 
 hipError_t launch_init(const SolveDev &s, const double2 *B, const int64_t *unit_idx,
                        const int32_t *seed_idx, int32_t limit, hipStream_t st);
-// one seed iteration (four launches, see kernels.hip)
-hipError_t launch_seed_iteration(const SolveDev &s, hipStream_t st);
 // the block's TB seed iterations in one launch (s.seed_block)
 hipError_t launch_seed_block(const SolveDev &s, hipStream_t st);
 // the block's TB seed iterations, in whichever form s asks for
