@@ -1903,9 +1903,12 @@ hipError_t launch_block_iterations(const SolveDev &s, hipStream_t st)
     if (s.seed_block) return launch_seed_block(s, st);
     // sums folded into k_rupd and k_pupd: three dependent launches an iteration instead of five.  One site
     // or a few of a lattice of 5,000 to 65,536 rows: 1.15 to 1.25 times faster per call, 16 x 6 right-hand
-    // sides in a batch 221 -> 206 ms, 128 of 16,384 rows 354 -> 345 ms, 256 of them equal.  Beyond 256
-    // tiles one wave's four loads are not enough, and the launches are long against the gaps.
-    const bool fold = !s.has_hub && s.n <= FOLD_TILES * WG;
+    // sides in a batch (about 6,800 tiles) 221 -> 206 ms, 128 of 16,384 rows (8,192 tiles) 354 -> 345 ms.
+    // With 256 of them (16,384 tiles) the sums that every wave repeats cost more than the launches: 13.84
+    // against 13.6 s per solve.  Beyond 256 tiles of one right-hand side one wave's four loads are not
+    // enough, and the launches are long against the gaps.
+    const int64_t tiles = s.it_rhs ? s.n_it_rhs : s.K * s.nblk;
+    const bool fold = !s.has_hub && s.n <= FOLD_TILES * WG && tiles <= FOLD_MAX_ITEMS;
     for (int t = 0; t < s.TB; ++t) {
         const hipError_t e = launch_seed_iteration(s, t, fold, st);
         if (e != hipSuccess) return e;

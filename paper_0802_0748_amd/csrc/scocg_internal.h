@@ -111,6 +111,8 @@ static constexpr int64_t RED_BIG_ROWS = 1 << 21;
 // Up to this many 256-row tiles (stored matrices) the seed reductions are folded into the kernels that
 // need them, which one wave sums with four loads per lane.
 static constexpr int64_t FOLD_TILES = 256;
+// ... and up to this many tiles over all right-hand sides (see launch_block_iterations).
+static constexpr int64_t FOLD_MAX_ITEMS = 8192;
 
 // Down-spin blocks of at most this many configurations take the LDS-tiled product (one 16-byte element
 // per configuration and a 0 for the fillers, 64 KB of LDS; a ring of 3 to 30 sites has no block of
