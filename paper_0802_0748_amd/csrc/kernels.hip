@@ -398,7 +398,7 @@ __device__ inline void fold_commit(const SolveDev &s, int t, int64_t j)
 //   k_alpha   alpha_n = rho_n / (p_n.q)                           (one workgroup per rhs)
 //   k_rupd    r_{n+1} = r_n - alpha_n q;  partial sums of r.r and |r|^2
 //   k_beta    rho_{n+1}, ||r_{n+1}||, beta_n, convergence of the seed (one workgroup per rhs)
-// With stored matrices of at most FOLD_TILES tiles it is three: k_rupd works out alpha_n itself, and
+// With stored matrices of at most FOLD_TILES tiles (and FOLD_MAX_ITEMS in all) it is three: k_rupd works out alpha_n itself, and
 // k_pupd of the next iteration beta_n (FOLD; the block's last iteration has both launches).
 // ---------------------------------------------------------------------------------------
 // k_pupd and k_rupd: one wave per 256-row tile, four rows per lane, so that a tile's sums need no LDS and
@@ -1905,7 +1905,7 @@ hipError_t launch_block_iterations(const SolveDev &s, hipStream_t st)
     // or a few of a lattice of 5,000 to 65,536 rows: 1.15 to 1.25 times faster per call, 16 x 6 right-hand
     // sides in a batch (about 6,800 tiles) 221 -> 206 ms, 128 of 16,384 rows (8,192 tiles) 354 -> 345 ms.
     // With 256 of them (16,384 tiles) the sums that every wave repeats cost more than the launches: 13.84
-    // against 13.6 s per solve.  Beyond 256 tiles of one right-hand side one wave's four loads are not
+    // against 13.67 s per solve with the launches.  Beyond 256 tiles of one right-hand side one wave's four loads are not
     // enough, and the launches are long against the gaps.
     const int64_t tiles = s.it_rhs ? s.n_it_rhs : s.K * s.nblk;
     const bool fold = !s.has_hub && s.n <= FOLD_TILES * WG && tiles <= FOLD_MAX_ITEMS;
