@@ -396,6 +396,15 @@ extern "C" int csr_upload(int64_t n, int64_t nnz, const int64_t *rp, const int64
     }
     d.ell_nnz = sptr[d.nslices];
     d.max_w = maxw;
+    d.chain[0] = maxw;
+    auto width = [&](int64_t q) -> int64_t { return q < d.nslices ? sw[q] : 0; };
+    for (int64_t q = 0; q < d.nslices; q += 4) {
+        const int64_t even = width(q) + width(q + 2), odd = width(q + 1) + width(q + 3);
+        const int64_t far = width(q + 64) + width(q + 65) + width(q + 66) + width(q + 67);
+        d.chain[1] = std::max(d.chain[1], std::max(even, odd));
+        d.chain[2] = std::max(d.chain[2], even + odd);
+        d.chain[3] = std::max(d.chain[3], even + odd + far);
+    }
     std::vector<int32_t> ecol(d.ell_nnz, 0);
     std::vector<double> eval(d.ell_nnz, 0.0);
     H->h_ell_src.assign(d.ell_nnz, -1);
@@ -844,8 +853,12 @@ int solve(SolveRequest &rq, hipStream_t st)
     s.spmv_rb = pairable ? 2 : 1;
     for (int64_t j = 0; j < K; ++j) (hdesc[j].hub ? s.has_hub : s.has_sell) = 1;
     for (int64_t j = 0; j < K; ++j) (hdesc[j].n >= RED_BIG_ROWS ? s.has_red_big : s.has_red_small) = 1;
-    for (int64_t j = 0; j < K; ++j) s.max_w = std::max(s.max_w, (rq.Hj.empty() ? rq.H : rq.Hj[j])->d.max_w);
-    s.seed_block = !s.has_hub && seed_block_fits(n, K);
+    s.seed_block = !s.has_hub && seed_block_holds(n, K);
+    for (int64_t j = 0; j < K; ++j) {
+        const DevCSR &dj = (rq.Hj.empty() ? rq.H : rq.Hj[j])->d;
+        s.max_w = std::max(s.max_w, dj.max_w);
+        s.seed_block = s.seed_block && seed_block_pays(dj.n, K, dj.ell_nnz, dj.max_w, dj.chain[seed_block_layout(n)]);
+    }
     s.hub_lds = 1;
     for (int64_t j = 0; j < K; ++j) {
         const DevCSR &dj = (rq.Hj.empty() ? rq.H : rq.Hj[j])->d;
@@ -1991,7 +2004,8 @@ extern "C" int greens_diag_noalloc(scocg_csr_t H, int64_t n_shift, const double 
     (d.d_hub ? s.has_hub : s.has_sell) = 1;
     (n >= RED_BIG_ROWS ? s.has_red_big : s.has_red_small) = 1;
     s.max_w = d.max_w;
-    s.seed_block = !s.has_hub && seed_block_fits(n, K);
+    s.seed_block = !s.has_hub && seed_block_holds(n, K) &&
+                   seed_block_pays(n, K, d.ell_nnz, d.max_w, d.chain[seed_block_layout(n)]);
     s.hub_lds = 1;
     if (d.d_hub) {
         if (d.hub_Dd > HUB_LDS_MAX || n / d.hub_Dd > (n + 255) / 256) s.hub_lds = 0;

@@ -1,6 +1,8 @@
 // Internal declarations shared by the HIP kernels and the host driver of libscocg.
 #pragma once
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 #include <stdint.h>
 
 namespace scocg {
@@ -91,19 +93,36 @@ struct HubbardOp {
     int32_t pad;
 };
 
-// Stored matrices of at most SEED_BLOCK_ROWS rows run a block's seed iterations in one launch, one
-// workgroup per right-hand side (seed_block.hip).  Larger ones, up to the 8192 rows whose p fits in
-// LDS (128 of 160 KB), do so from SEED_BLOCK_RHS right-hand sides on: there one workgroup
-// streams a matrix of over half a megabyte through its L2 port each iteration, which takes longer
-// than the five launches for one right-hand side (cubic 20^3: 20 against 16 us) but the same
-// time for up to 256 of them (23 against 60 us at 128).
+// Stored matrices of at most SEED_BLOCK_ROWS rows, up to the 8192 rows whose p fits in LDS (128 of
+// 160 KB) from SEED_BLOCK_RHS right-hand sides on, can run a block's seed iterations in one launch, one
+// workgroup per right-hand side (seed_block.hip): there fewer right-hand sides leave the chip idle
+// (6000 rows of 17 entries: 128 of them 4.6 ms per 96 iterations against 5.4 ms in three launches an
+// iteration; cubic 20^3, one of them: 20 us an iteration against 16).
 static constexpr int64_t SEED_BLOCK_ROWS = 4096;
 static constexpr int64_t SEED_BLOCK_ROWS_MANY = 8192;
 static constexpr int64_t SEED_BLOCK_RHS = 128;
-inline bool seed_block_fits(int64_t n, int64_t K)
+inline bool seed_block_holds(int64_t n, int64_t K)
 {
     return n <= SEED_BLOCK_ROWS || (n <= SEED_BLOCK_ROWS_MANY && K >= SEED_BLOCK_RHS);
 }
+// A workgroup streams its matrix every iteration: 0.148 ns a stored slot, or, where the slots are uneven,
+// the longest chain of one wave (its slices' widths, one after the other), a step of it 500 slots'
+// time.  The launches spread the slots over the chip: their time is that of 440 slots per entry of the
+// widest row, of 810 per entry of the mean row for two right-hand sides and more (two share a
+// thread), or, once the chip is full, of slots * K / 154; and they cost about 9 us more per iteration,
+// 60,000 slots.  us per iteration, one launch against three: 4096 rows of 9 entries 12 / 16, of 17
+// 17.3 / 16.5, of 65 45 / 20, of 257 163 / 33; 256 of them of 200 entries 78 / 31; one of them dense
+// 305 / 215; for 16 right-hand sides 17 entries 18 / 22, 33 27 / 24; for 256 65 entries 57 / 97; 2048
+// rows of 33 entries 17.7 / 17.5; 1024 rows of 65 entries 15.7 / 19.4, of 257 45 / 32.
+inline bool seed_block_pays(int64_t n, int64_t K, int64_t slots, int64_t max_w, int64_t chain)
+{
+    const int64_t one = std::max(slots, 500 * chain);
+    const int64_t chip = std::max(std::max(440 * max_w, K > 1 ? 810 * slots / n : 0), slots * K / 154);
+    return one - chip <= 60000;
+}
+// The slices of a wave when the longest right-hand side of the call has n rows: 0 to 3 for one slice, two
+// (every other one of a 256-row tile), a tile, two tiles (t and t + 16).
+inline int seed_block_layout(int64_t n) { return n <= 1024 ? 0 : n <= 2048 ? 1 : n <= SEED_BLOCK_ROWS ? 2 : 3; }
 
 // Right-hand sides of at least this many rows sum their seed reductions with 1024 threads.
 static constexpr int64_t RED_BIG_ROWS = 1 << 21;
@@ -138,6 +157,7 @@ struct DevCSR {
     int64_t *h_col;
     int64_t *h_ell_src;   // [ell_nnz] CSR position of each slot (host)
     int max_w;            // widest slice
+    int64_t chain[4];     // most slots of a wave in one row after the other (see seed_block_layout)
     HubbardOp *d_hub;     // matrix-free operator (device struct), or null for a stored matrix
     void *d_hub_tables;   // device tables the operator points into
     int64_t hub_Dd;       // its down-spin configurations (host copy)

@@ -1,0 +1,66 @@
+"""Which kernels a call launches, on the host: the library runs on a runtime that records launches."""
+
+import pytest
+
+from host_library import run
+
+_SEED_BLOCK = """
+def one_launch(K, *matrices):
+    seen = []
+    Hs = [upload(*m)[1] for m in matrices]
+    if len(Hs) == 1:
+        for entry in ('greens_diag', 'greens_diag_noalloc')[:1 if K * len(matrices[0][0]) > 60000 else 2]:
+            fake.fake_forget()
+            assert greens(Hs[0], K, entry=entry) == C.OK, lib.scocg_last_error()
+            seen.append(launched('k_seed_block') > 0)
+            assert seen[-1] != (launched('k_spmv') > 0)
+    else:
+        fake.fake_set_word(SEED_STOPPED)
+        fake.fake_forget()
+        h = (ctypes.c_void_p * len(Hs))(*[H.value for H in Hs])
+        nr = np.full(len(Hs), K // len(Hs), dtype=np.int64)
+        idx = np.zeros(K, dtype=np.int64)
+        z, o = np.array([0.5j]), C.Opts()
+        lib.scocg_default_opts(ctypes.byref(o))
+        assert lib.greens_diag_batched(len(Hs), h, nr.ctypes.data, idx.ctypes.data, 1, z.ctypes.data, ctypes.byref(o),
+                                       OUT, None, None) == C.OK
+        seen.append(launched('k_seed_block') > 0)
+    for H in Hs:
+        lib.csr_free(H)
+    assert len(set(seen)) == 1, seen
+    return seen[0]
+
+
+def uneven(n, heavy, width):
+    # a band of 7 entries whose first `heavy` rows (and the columns of the same numbers) have `width`
+    # entries more, spread over the columns
+    rp, col, val = band(n, 7)
+    rows = [set(col[rp[i]:rp[i + 1]]) for i in range(n)]
+    for i in range(heavy):
+        for j in (i + np.arange(width) * (n // width)) % n:
+            rows[i].add(j)
+            rows[j].add(i)
+    rows = [sorted(r) for r in rows]
+    rp = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int64)
+    col = np.concatenate(rows).astype(np.int64)
+    return rp, col, np.ones(len(col))
+
+"""
+
+
+@pytest.mark.parametrize("what,one", [
+    # narrow rows, and wide ones of few rows: one workgroup's stream is short
+    ("1, band(4096, 9)", True), ("4, band(4096, 17)", True), ("1, band(512, 511)", True), ("1, band(1024, 65)", True),
+    ("16, band(1024, 257)", True),
+    # wide rows that the launches spread over the chip
+    ("1, band(4096, 33)", False), ("1, band(2048, 129)", False), ("16, band(4096, 65)", False),
+    ("64, band(4096, 257)", False), ("1, band(1024, 257)", False), ("1, uneven(4096, 1, 4096)", False),
+    # uneven rows: a wave's chain of slots is longer than the mean
+    ("1, uneven(4096, 64, 200)", True), ("1, uneven(4096, 256, 200)", False), ("1, uneven(2048, 256, 400)", False),
+    # until there are enough right-hand sides for the whole chip
+    ("256, band(4096, 257)", True), ("128, band(6000, 33)", True), ("128, band(6000, 129)", False),
+    ("127, band(6000, 7)", False),
+    # one wide matrix of a batch is enough
+    ("2, band(300, 7), band(4000, 129)", False), ("2, band(300, 7), band(4000, 7)", True)])
+def test_one_launch_iterations_only_where_one_workgroup_streams_as_fast(what, one, tmp_path):
+    run(_SEED_BLOCK + f"assert one_launch({what}) is {one}", tmp_path)
