@@ -1524,8 +1524,7 @@ extern "C" int krylov_greens_vec(scocg_csr_t H, int64_t n_shift, const double *z
     A(bst, 2 * sizeof(LzRhs));
     A(bz, (size_t)n_shift * sizeof(double2));
     A(bscal, 8 * sizeof(double));
-    // a matrix-free operator with blocks of the tiled product's sizes
-    const bool tiled = H->d.d_hub && lz_hub_fits(H->d.hub_Dd);
+    const bool tiled = H->d.d_hub && lz_hub_fits(n, H->d.hub_Dd);
     DevBuf bedge;
     if (tiled) A(bedge, (size_t)(n / H->d.hub_Dd) * LZ_TILE * sizeof(double));
     if (e != hipSuccess) return fail(SCOCG_ENOMEM, std::string("device allocation failed: ") + hipGetErrorString(e));
@@ -1622,8 +1621,7 @@ extern "C" int ground_state(scocg_csr_t H, const double *x0, int32_t nu, double 
     A(bscal, 8 * sizeof(double));
     A(bzb, n * sizeof(double2));
     A(bzx, n * sizeof(double2));
-    // a matrix-free operator with blocks of the tiled product's sizes
-    const bool tiled = H->d.d_hub && lz_hub_fits(H->d.hub_Dd);
+    const bool tiled = H->d.d_hub && lz_hub_fits(n, H->d.hub_Dd);
     DevBuf bedge;
     if (tiled) A(bedge, (size_t)(n / H->d.hub_Dd) * LZ_TILE * sizeof(double));
     if (e != hipSuccess) return fail(SCOCG_ENOMEM, std::string("device allocation failed: ") + hipGetErrorString(e));

@@ -56,13 +56,21 @@ struct LzDev {
     double gscale;       // G is scaled by this: 1 for unit start vectors, |b|^2 for a start vector b
 };
 
-// Down-spin blocks the tiled product takes (krylov.hip: k_lz_hub): a 256-row tile may touch two
-// blocks at most, and a block with its tiles' ends fits four rows per thread.
-inline bool lz_hub_fits(int64_t Dd) { return Dd >= 256 && Dd <= 4 * 1024 - 255; }
-
 // The sums of a step are folded into the kernels that need them (krylov.hip: k_lz_matvec, k_lz_axpy)
 // up to this many tiles, which one wave sums with four loads per lane.
 constexpr int64_t LZ_FOLD_TILES = 256;
+
+// Operators the tiled product takes (krylov.hip: k_lz_hub): a 256-row tile may touch two down-spin blocks
+// at most, a block with its tiles' ends fits four rows per thread, and the sector is beyond the folded
+// sums.  Below, its five launches a step lose to the general product's two, most of all where few
+// up-spin configurations leave most of the chip idle: 200 steps of 14 sites with 1 + 7 electrons (14
+// blocks of 3432) 5.2 ms against 2.9, 11 sites with 1 + 5 (11 of 462) 3.8 against 2.6, 12 sites with
+// 2 + 6 (66 of 924) 4.4 against 3.0; above, 13 sites with 2 + 6 (78 of 1716) 4.7 against 5.0 in four
+// launches, 14 sites with 3 + 7 (364 of 3432) 8.6 against 13.4.
+inline bool lz_hub_fits(int64_t n, int64_t Dd)
+{
+    return Dd >= 256 && Dd <= 4 * 1024 - 255 && (n + LZ_TILE - 1) / LZ_TILE > LZ_FOLD_TILES;
+}
 
 // Single real vector of n rows on the stored matrix or the matrix-free operator; one partial
 // per 256-row tile, summed in fixed order by one workgroup into the device scalars scal[].

@@ -805,7 +805,7 @@ hipError_t launch_lanczos_step(const LzDev &s0, int n, hipStream_t st)
     // up to LZ_FOLD_TILES tiles the sums are worked out by the kernels that need them: two launches a
     // step instead of four (256 right-hand sides on 16,384 rows: the
     // two sums' launches were 10 of 72 us a step; 95 on 1,176 rows: 22.6 -> 15 us a step)
-    if (s.nblk <= LZ_FOLD_TILES && !s.edge) {
+    if (s.nblk <= LZ_FOLD_TILES) {
         if (s.rb == 1) {
             hipLaunchKernelGGL((k_lz_matvec<1, true, false>), gv, dim3(WG), 0, st, s, n);
             hipLaunchKernelGGL((k_lz_axpy<1, true>), gv, dim3(WG), 0, st, s, n);
@@ -818,7 +818,7 @@ hipError_t launch_lanczos_step(const LzDev &s0, int n, hipStream_t st)
         return hipGetLastError();
     }
     if (s.edge) {
-        if (!s.hub || s.rb != 1 || !lz_hub_fits(s.hub_Dd) || s.hub_Dd * s.hub_Du != s.n || s.hub_Du > 0x7ffffff0LL)
+        if (!s.hub || s.rb != 1 || !lz_hub_fits(s.n, s.hub_Dd) || s.hub_Dd * s.hub_Du != s.n || s.hub_Du > 0x7ffffff0LL)
             return hipErrorInvalidValue;
         const dim3 gh((unsigned)(8 * hub_stretch(s.hub_Du)));
         const int64_t span = s.hub_Dd + LZ_TILE - 1;  // rows from a block's first tile on, at most

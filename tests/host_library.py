@@ -66,6 +66,7 @@ def greens(H, K, M=2, entry='greens_diag', **opts):
 
 
 def krylov_vec(H, nu=2):
+    fake.fake_set_word(1)  # (the start vector's norm is not zero)
     z = np.array([0.5j])
     return lib.krylov_greens_vec(H, 1, z.ctypes.data, OUT, nu, OUT, None, None, None)
 """

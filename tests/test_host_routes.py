@@ -64,3 +64,22 @@ def uneven(n, heavy, width):
     ("2, band(300, 7), band(4000, 129)", False), ("2, band(300, 7), band(4000, 7)", True)])
 def test_one_launch_iterations_only_where_one_workgroup_streams_as_fast(what, one, tmp_path):
     run(_SEED_BLOCK + f"assert one_launch({what}) is {one}", tmp_path)
+
+
+_TILED = """
+def tiled(L, n_up, n_dn):
+    H = hubbard(L, n_up, n_dn)
+    fake.fake_forget()
+    assert krylov_vec(H) == C.OK, lib.scocg_last_error()
+    assert (launched('k_lz_hub') > 0) != (launched('k_lz_matvec') > 0)
+    return launched('k_lz_hub') > 0
+
+"""
+
+
+@pytest.mark.parametrize("sector,is_tiled", [
+    # up to 65,536 rows the general product folds its sums: two launches a step instead of five
+    ("11, 0, 5", False), ("11, 1, 5", False), ("14, 1, 7", False), ("12, 2, 6", False), ("13, 2, 6", True), ("11, 5, 5", True),
+    ("14, 3, 7", True), ("10, 5, 5", False), ("16, 2, 8", False)])
+def test_tiled_lanczos_steps_only_beyond_the_folded_sums(sector, is_tiled, tmp_path):
+    run(_TILED + f"assert tiled({sector}) is {is_tiled}", tmp_path)
