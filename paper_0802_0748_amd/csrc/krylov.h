@@ -59,6 +59,7 @@ struct LzDev {
 // The sums of a step are folded into the kernels that need them (krylov.hip: k_lz_matvec, k_lz_axpy)
 // up to this many tiles, which one wave sums with four loads per lane.
 constexpr int64_t LZ_FOLD_TILES = 256;
+constexpr int LZ_HUB_THREADS = 1024;  // of a workgroup of the tiled product
 
 // Operators the tiled product takes (krylov.hip: k_lz_hub): a 256-row tile may touch two down-spin blocks
 // at most, a block with its tiles' ends fits four rows per thread, and the sector is beyond the folded
@@ -66,10 +67,13 @@ constexpr int64_t LZ_FOLD_TILES = 256;
 // up-spin configurations leave most of the chip idle: 200 steps of 14 sites with 1 + 7 electrons (14
 // blocks of 3432) 5.2 ms against 2.9, 11 sites with 1 + 5 (11 of 462) 3.8 against 2.6, 12 sites with
 // 2 + 6 (66 of 924) 4.4 against 3.0; above, 13 sites with 2 + 6 (78 of 1716) 4.7 against 5.0 in four
-// launches, 14 sites with 3 + 7 (364 of 3432) 8.6 against 13.4.
+// launches, 14 sites with 3 + 7 (364 of 3432) 8.6 against 13.4.  And a launch
+// has fewer than 2^32 threads along x, which 4.5 million blocks (1.3e9 rows at 300 down-spin
+// configurations) exceed; the general product has one thread per row.
 inline bool lz_hub_fits(int64_t n, int64_t Dd)
 {
-    return Dd >= 256 && Dd <= 4 * 1024 - 255 && (n + LZ_TILE - 1) / LZ_TILE > LZ_FOLD_TILES;
+    if (Dd < 256 || Dd > 4 * 1024 - 255 || (n + LZ_TILE - 1) / LZ_TILE <= LZ_FOLD_TILES) return false;
+    return (n / Dd + 7) / 8 * 8 * LZ_HUB_THREADS < (1LL << 32);
 }
 
 // Single real vector of n rows on the stored matrix or the matrix-free operator; one partial

@@ -286,9 +286,9 @@ __global__ void __launch_bounds__(WG, 8) k_lz_matvec(LzDev s, int n)
 // at a time, 192 us here (the hops one per lane, taken with readlane, and the tiles' sums in the same
 // kernel: 284 us before those two; 224 while the basis vectors were also written out).
 template <int RPT>
-__global__ void __launch_bounds__(1024, 8) k_lz_hub(LzDev s, int n)
+__global__ void __launch_bounds__(LZ_HUB_THREADS, 8) k_lz_hub(LzDev s, int n)
 {
-    constexpr int NT = 1024;
+    constexpr int NT = LZ_HUB_THREADS;
     constexpr int HC = RPT == 4 ? 3 : 8 / RPT;             // up-spin hops gathered at once
     constexpr int SC = 8;                                  // down-spin hops read at once
     __shared__ double xl[NT * RPT + 1];  // xl[Dd] = 0 for the fillers
@@ -818,13 +818,13 @@ hipError_t launch_lanczos_step(const LzDev &s0, int n, hipStream_t st)
         return hipGetLastError();
     }
     if (s.edge) {
-        if (!s.hub || s.rb != 1 || !lz_hub_fits(s.n, s.hub_Dd) || s.hub_Dd * s.hub_Du != s.n || s.hub_Du > 0x7ffffff0LL)
+        if (!s.hub || s.rb != 1 || !lz_hub_fits(s.n, s.hub_Dd) || s.hub_Dd * s.hub_Du != s.n)
             return hipErrorInvalidValue;
         const dim3 gh((unsigned)(8 * hub_stretch(s.hub_Du)));
         const int64_t span = s.hub_Dd + LZ_TILE - 1;  // rows from a block's first tile on, at most
-        if (span <= 1024) hipLaunchKernelGGL(k_lz_hub<1>, gh, dim3(1024), 0, st, s, n);
-        else if (span <= 2048) hipLaunchKernelGGL(k_lz_hub<2>, gh, dim3(1024), 0, st, s, n);
-        else hipLaunchKernelGGL(k_lz_hub<4>, gh, dim3(1024), 0, st, s, n);
+        if (span <= 1024) hipLaunchKernelGGL(k_lz_hub<1>, gh, dim3(LZ_HUB_THREADS), 0, st, s, n);
+        else if (span <= 2048) hipLaunchKernelGGL(k_lz_hub<2>, gh, dim3(LZ_HUB_THREADS), 0, st, s, n);
+        else hipLaunchKernelGGL(k_lz_hub<4>, gh, dim3(LZ_HUB_THREADS), 0, st, s, n);
         hipLaunchKernelGGL(k_lz_edge, dim3((unsigned)((s.hub_Du + 3) / 4)), dim3(WG), 0, st, s);
     } else if (s.rb == 1) hipLaunchKernelGGL((k_lz_matvec<1, false, false>), gv, dim3(WG), 0, st, s, n);
     else if (n == 0) hipLaunchKernelGGL((k_lz_matvec<LZ_RB, false, true>), gv, dim3(WG), 0, st, s, n);

@@ -83,3 +83,14 @@ def tiled(L, n_up, n_dn):
     ("14, 3, 7", True), ("10, 5, 5", False), ("16, 2, 8", False)])
 def test_tiled_lanczos_steps_only_beyond_the_folded_sums(sector, is_tiled, tmp_path):
     run(_TILED + f"assert tiled({sector}) is {is_tiled}", tmp_path)
+
+
+def test_launches_of_the_tiled_step_stay_below_2_32_threads(tmp_path):
+    """25 sites with 11 + 2 electrons: 4.5 million blocks of 1024 threads would be one launch of more than
+    2^32 threads along x, which the runtime refuses; the general step takes the sector."""
+    run("""
+H = hubbard(25, 11, 2)
+assert krylov_vec(H, 1) == C.OK
+assert launched('k_lz') > 0
+assert max(fake.fake_threads_x(i) for i in range(fake.fake_launches())) < 1 << 32
+""", tmp_path)
