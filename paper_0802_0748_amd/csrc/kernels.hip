@@ -1053,7 +1053,7 @@ __global__ void __launch_bounds__(NT) k_beta(SolveDev s)
 // (two complex multiply-adds per step instead of three for p^k directly).  The kernel
 // writes (a'_n, b'_n) for every step of the block in which the pair is still active.
 //
-// A workgroup of 16 P threads takes P shifts of one rhs.  Only the recurrence of pi is serial: P
+// A workgroup of 16 P threads takes P shifts of one rhs (a row of the grid).  Only the recurrence of pi is serial: P
 // lanes run it over the block (about five dependent operations a step, pi_n kept in LDS), and
 // everything that hangs off it (the residual and the stopping test, the quotients and (a'_n, b'_n))
 // is one item per pair and step over all threads, written with consecutive steps in consecutive
@@ -1076,9 +1076,8 @@ __global__ void __launch_bounds__(P == 16 ? 256 : 512) k_pair_scalars(SolveDev s
     __shared__ int live[P];
     __shared__ unsigned long long st_bytes, st_flops;
     __shared__ unsigned int st_count;
-    const int64_t per = (s.M + P - 1) / P;
-    const int64_t j = blockIdx.x / per;
-    const int64_t k0 = (blockIdx.x - j * per) * P;
+    const int64_t j = blockIdx.y;
+    const int64_t k0 = (int64_t)blockIdx.x * P;
     const int64_t p0 = j * s.M + k0;  // first pair
     const int tid = threadIdx.x;
     const int npair = (int)min((int64_t)P, s.M - k0);
@@ -1920,7 +1919,7 @@ hipError_t launch_pair_scalars(const SolveDev &s, hipStream_t st)
 {
     // 16 shifts per workgroup until there are enough workgroups for the chip several times over
     const bool wide = s.K * ((s.M + 15) / 16) > 1024;
-    const dim3 g((unsigned)(s.K * ((s.M + (wide ? 63 : 15)) / (wide ? 64 : 16))));
+    const dim3 g = grid2((s.M + (wide ? 63 : 15)) / (wide ? 64 : 16), s.K);
     if (wide) {
         if (s.precision == 0) hipLaunchKernelGGL((k_pair_scalars<double2, 64>), g, dim3(512), 0, st, s);
         else hipLaunchKernelGGL((k_pair_scalars<float2, 64>), g, dim3(512), 0, st, s);

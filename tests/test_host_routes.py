@@ -94,3 +94,16 @@ assert krylov_vec(H, 1) == C.OK
 assert launched('k_lz') > 0
 assert max(fake.fake_threads_x(i) for i in range(fake.fake_launches())) < 1 << 32
 """, tmp_path)
+
+
+def test_launch_of_the_shift_scalars_does_not_grow_along_x_with_the_right_hand_sides(tmp_path):
+    """8 threads of it per pair, counted along x, would pass 2^32 at 5.4e8 pairs (one thread per pair, as the
+    other launches have, at 4.3e9)."""
+    run("""
+_, H = upload(*band(64, 3))
+for K, M in ((3, 5), (3000, 64), (65535, 2), (2, 70000)):
+    fake.fake_forget()
+    greens(H, K, M, block=1)
+    x = [fake.fake_threads_x(i) for i in range(fake.fake_launches()) if b'k_pair_scalars' in fake.fake_name(i)]
+    assert x and max(x) <= 16 * (M + 63), (K, M, max(x))
+""", tmp_path)
