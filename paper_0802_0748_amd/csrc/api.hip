@@ -351,7 +351,7 @@ static void free_dev(DevCSR &d)
 template <typename T>
 static hipError_t upload(T **dst, const T *src, size_t count, hipStream_t st)
 {
-    hipError_t e = hipMalloc((void **)dst, std::max<size_t>(count, 1) * sizeof(T));
+    hipError_t e = keeper().fresh(std::max<size_t>(count, 1) * sizeof(T), (void **)dst);
     if (e != hipSuccess) return e;
     if (count == 0) return hipSuccess;
     e = hipMemcpyAsync(*dst, src, count * sizeof(T), hipMemcpyHostToDevice, st);
