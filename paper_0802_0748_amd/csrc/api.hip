@@ -71,6 +71,12 @@ static bool device_ok(const void *p)
 class Keeper {
 public:
     static constexpr size_t KEEP_MIN = 1ull << 20, KEEP_MAX = 256ull << 20, KEEP_BYTES = 1ull << 30;
+    static constexpr size_t KEEP_PINNED = 8;
+    Keeper()
+    {
+        free_.reserve(KEEP_BYTES / KEEP_MIN + 64);
+        pinned_.reserve(KEEP_PINNED);
+    }
     static bool keeps(size_t bytes) { return bytes >= KEEP_MIN && bytes <= KEEP_MAX; }
     hipError_t take(size_t bytes, void **ptr, size_t *got, int *dev)
     {
@@ -104,24 +110,19 @@ public:
         }
         return e;
     }
+    // (called from destructors, which may not throw: the lists never grow past what they reserve)
     void give(void *ptr, size_t bytes, int dev)
     {
-        std::vector<void *> out;
         {
             std::lock_guard<std::mutex> lock(mu_);
-            if (live_ == 0) {
-                out.push_back(ptr);
-            } else {
+            if (live_ > 0 && free_.size() < free_.capacity()) {
                 free_.push_back({ptr, bytes, dev});
                 held_ += bytes;
-                while (held_ > KEEP_BYTES) {
-                    out.push_back(free_.front().ptr);
-                    held_ -= free_.front().bytes;
-                    free_.erase(free_.begin());
-                }
+                ptr = nullptr;
             }
         }
-        for (void *q : out) (void)hipFree(q);
+        if (ptr) (void)hipFree(ptr);
+        else shrink(KEEP_BYTES);
     }
     void *take_pinned(size_t bytes)
     {
@@ -137,22 +138,24 @@ public:
     bool give_pinned(void *ptr, size_t bytes)
     {
         std::lock_guard<std::mutex> lock(mu_);
-        if (live_ == 0 || pinned_.size() >= 8 || bytes > (4ull << 20)) return false;
+        if (live_ == 0 || pinned_.size() >= KEEP_PINNED || bytes > (4ull << 20)) return false;
         pinned_.push_back({ptr, bytes, 0});
         return true;
     }
+    // gives back every kept block; whether there was device memory among them
     bool drop()
     {
-        std::vector<Block> out, host;
-        {
-            std::lock_guard<std::mutex> lock(mu_);
-            out.swap(free_);
-            host.swap(pinned_);
-            held_ = 0;
+        const bool any = shrink(0);
+        for (;;) {
+            void *host = nullptr;
+            {
+                std::lock_guard<std::mutex> lock(mu_);
+                if (pinned_.empty()) return any;
+                host = pinned_.back().ptr;
+                pinned_.pop_back();
+            }
+            (void)hipHostFree(host);
         }
-        for (const Block &b : out) (void)hipFree(b.ptr);
-        for (const Block &b : host) (void)hipHostFree(b.ptr);
-        return !out.empty();
     }
     void matrix_up()
     {
@@ -175,6 +178,21 @@ private:
         size_t bytes;
         int dev;
     };
+    // gives back device blocks, the oldest first, until at most `most` bytes are kept
+    bool shrink(size_t most)
+    {
+        for (bool any = false;; any = true) {
+            void *old = nullptr;
+            {
+                std::lock_guard<std::mutex> lock(mu_);
+                if (held_ <= most) return any;
+                old = free_.front().ptr;
+                held_ -= free_.front().bytes;
+                free_.erase(free_.begin());
+            }
+            (void)hipFree(old);
+        }
+    }
     std::mutex mu_;
     std::vector<Block> free_, pinned_;
     size_t held_ = 0;

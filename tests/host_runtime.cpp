@@ -27,6 +27,13 @@ int frees = 0, refused = 0;
 uint32_t word = 0;
 int new_fails_after_sync = 0;
 thread_local bool new_fails = false;
+// the runtime's own records
+struct Recording {
+    std::lock_guard<std::mutex> lock{mu};
+    bool was = new_fails;
+    Recording() { new_fails = false; }
+    ~Recording() { new_fails = was; }
+};
 // one object stands for every stream, event and graph
 char handle;
 }  // namespace
@@ -49,7 +56,7 @@ uint64_t fake_threads_x(int i) { return (uint64_t)launches[i].grid.x * launches[
 // ---- the runtime ----
 hipError_t hipMalloc(void **ptr, size_t size)
 {
-    std::lock_guard<std::mutex> lock(mu);
+    Recording rec;
     if (live + size > limit) {
         ++refused;
         return hipErrorOutOfMemory;
@@ -62,7 +69,7 @@ hipError_t hipMalloc(void **ptr, size_t size)
 }
 hipError_t hipFree(void *ptr)
 {
-    std::lock_guard<std::mutex> lock(mu);
+    Recording rec;
     auto b = blocks.find((uintptr_t)ptr);
     if (b == blocks.end()) abort();
     live -= b->second;
@@ -150,7 +157,7 @@ hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *shared, hi
 }
 hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **, size_t, hipStream_t)
 {
-    std::lock_guard<std::mutex> lock(mu);
+    Recording rec;
     launches.push_back({names[f], grid, block});
     return hipSuccess;
 }
