@@ -26,6 +26,11 @@
  *  - Every call returns a status: SCOCG_OK, or one of the codes below; the
  *    message of the last failure on the calling thread is scocg_last_error().
  *    No C++ exception crosses the ABI.
+ *  - While any matrix or tape lives, work buffers of 1 to 256 MiB stay allocated between calls,
+ *    1 GiB in all at most (and up to 8 pinned host buffers of at most 4 MiB), for the calls that
+ *    follow.  The library frees them itself when an allocation of its own fails or the last matrix
+ *    and tape are released; a program that needs the memory elsewhere, or finds another allocator
+ *    out of memory, calls scocg_release_workspace().
  *  - All computation runs on the GPU.  There is no CPU fallback.
  */
 #ifndef SCOCG_H
@@ -381,6 +386,10 @@ typedef struct {
 int scocg_last_timing(scocg_timing *t);
 /* 1: record per-launch events around the update kernel (adds a small overhead). */
 void scocg_set_profiling(int on);
+
+/* Frees every work buffer kept between calls (see above); calls in progress on other threads keep
+ * theirs.  Later calls allocate anew. */
+void scocg_release_workspace(void);
 
 /*
  * Seed switches (Sec. 3.3) of right-hand side `rhs` in the most recent solve on this thread

@@ -7,7 +7,8 @@ PyTorch used for device memory, streams and autograd.
 
 from .api import (Hamiltonian, Tape, backward, contour, csr_validate, density_matrix_energy, greens_diag, greens_diag_noalloc,
                   greens_diag_batched, greens_diag_waves, greens_proj, ground_state, hubbard_fermion_op,
-                  krylov_greens_diag, krylov_greens_vec, last_switches, last_timing, options, set_profiling, shifted_cocg_solve)
+                  krylov_greens_diag, krylov_greens_vec, last_switches, last_timing, options, release_workspace, set_profiling,
+                  shifted_cocg_solve)
 
 __all__ = [
     "Hamiltonian",
@@ -28,6 +29,7 @@ __all__ = [
     "last_switches",
     "last_timing",
     "options",
+    "release_workspace",
     "set_profiling",
     "shifted_cocg_solve",
 ]

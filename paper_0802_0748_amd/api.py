@@ -187,6 +187,11 @@ def set_profiling(on: bool) -> None:
     C.load().scocg_set_profiling(int(bool(on)))
 
 
+def release_workspace() -> None:
+    """Free the work buffers the library keeps between calls (at most 1 GiB while a matrix or tape lives)."""
+    C.load().scocg_release_workspace()
+
+
 def _allowed(allow_noconv, allow_breakdown):
     a = [C.OK]
     if allow_noconv:

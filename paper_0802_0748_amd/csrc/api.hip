@@ -65,7 +65,8 @@ static bool device_ok(const void *p)
 // about their size: freeing and allocating them again took 1.3 of the 3.1 ms of a 128-row energy
 // with gradient (hipFree 1.0 ms, hipMalloc 0.3 ms; smaller blocks cost half a microsecond, and
 // beyond 256 MiB a call's own time hides it).  At most KEEP_BYTES stay, the oldest go first; all go
-// when the last matrix (or tape) is released or an allocation fails.  A block comes back only after
+// when the last matrix (or tape) is released, an allocation fails, or the caller asks
+// (scocg_release_workspace).  A block comes back only after
 // the stream of its call has drained, so whoever takes it next, on any thread or stream, finds
 // it idle; contents are never relied on.
 class Keeper {
@@ -704,6 +705,8 @@ extern "C" int scocg_last_timing(scocg_timing *t)
 }
 
 extern "C" void scocg_set_profiling(int on) { g_profiling = on ? 1 : 0; }
+
+extern "C" void scocg_release_workspace(void) { (void)keeper().drop(); }
 
 extern "C" int32_t scocg_last_switches(int64_t rhs, int32_t *log, int32_t max_entries)
 {

@@ -49,3 +49,15 @@ assert 900 << 20 <= fake.fake_live() - matrix <= (1 << 30) + (1 << 20)
 lib.csr_free(H)
 assert fake.fake_live() == 0
 """, tmp_path)
+
+
+def test_a_caller_gets_the_kept_buffers_back(tmp_path):
+    run("""
+_, H = upload(*band(200000, 3))
+matrix = fake.fake_live()
+assert krylov_vec(H) == C.OK
+assert fake.fake_live() > matrix
+lib.scocg_release_workspace()
+assert fake.fake_live() == matrix
+assert krylov_vec(H) == C.OK
+""", tmp_path)
