@@ -1973,7 +1973,7 @@ extern "C" int greens_diag_noalloc(scocg_csr_t H, int64_t n_shift, const double 
         L.swlog = (int32_t *)c.take(KM * 2 * sizeof(int32_t));
         L.flag = (int32_t *)c.take(sizeof(int32_t));
         L.worst = (int32_t *)c.take(sizeof(int32_t));
-        L.totals = (long long *)c.take(2 * sizeof(long long));
+        L.totals = (long long *)c.take(3 * sizeof(long long));
         L.rep = (PairReportDev *)c.take(KM * sizeof(PairReportDev));
         return c.off;
     };
@@ -2079,7 +2079,7 @@ extern "C" int greens_diag_noalloc(scocg_csr_t H, int64_t n_shift, const double 
     HIPCHK(launch_zero(L.stats, 3 * sizeof(unsigned long long), st));
     HIPCHK(launch_zero(L.swlog, KM * 2 * sizeof(int32_t), st));
     HIPCHK(launch_zero(L.worst, sizeof(int32_t), st));
-    HIPCHK(launch_zero(L.totals, 2 * sizeof(long long), st));
+    HIPCHK(launch_zero(L.totals, 3 * sizeof(long long), st));
     HIPCHK(launch_zero(s.p, 2 * ntot * sizeof(double2), st));
     HIPCHK(launch_init(s, nullptr, L.idx, L.sd, limit, st));
 
@@ -2093,7 +2093,8 @@ extern "C" int greens_diag_noalloc(scocg_csr_t H, int64_t n_shift, const double 
     }
     // (with the block's iterations in one launch the look, about 30 us, is a sixth of a block: taken
     // every fourth one, blocks past the last cost their empty launches)
-    const int per_sync = s.seed_block ? std::max(4, 64 / TB) : std::max(1, 64 / TB);
+    const int round = std::max(1, 64 / TB);  // blocks of a round, as solve() counts them
+    const int per_sync = s.seed_block ? std::max(4, round) : round;
     const int64_t max_blocks = (int64_t)K * ((int64_t)limit + 4 * M + 8) + 8 + per_sync;
     int64_t blocks = 0;
     for (;;) {
@@ -2116,7 +2117,7 @@ extern "C" int greens_diag_noalloc(scocg_csr_t H, int64_t n_shift, const double 
     HIPCHK(launch_gather_diag(s, L.idx, (double2 *)G, st));
     HIPCHK(launch_pack_report(K, M, s.fixed, L.iters, L.pst, L.res, L.seed, L.rep, L.worst, L.totals, st));
     int32_t worst = 0;
-    long long totals[2] = {0, 0};
+    long long totals[3] = {0, 0, 0};
     unsigned long long stats[3] = {0, 0, 0};
     HIPCHK(hipMemcpyAsync(&worst, L.worst, sizeof(int32_t), hipMemcpyDeviceToHost, st));
     HIPCHK(hipMemcpyAsync(totals, L.totals, sizeof(totals), hipMemcpyDeviceToHost, st));
@@ -2126,7 +2127,7 @@ extern "C" int greens_diag_noalloc(scocg_csr_t H, int64_t n_shift, const double 
     g_timing.total_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t_start).count();
     g_timing.iterations = totals[0];
     g_timing.switches = totals[1];
-    g_timing.blocks = blocks;
+    g_timing.blocks = (std::max<int64_t>(totals[2], 1) + round - 1) / round * round;
     g_timing.update_bytes = (double)stats[0];
     g_timing.update_flops = (double)stats[2];
     if (worst == 2) return fail(SCOCG_EBREAKDOWN, "COCG breakdown on at least one pair");

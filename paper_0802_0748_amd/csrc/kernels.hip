@@ -307,6 +307,7 @@ __global__ void __launch_bounds__(WG) k_init(SolveDev s, const double2 *__restri
         st.sw_target = -1;
         st.n_active = nb > 0 ? (int32_t)s.M : 0;
         st.switches = 0;
+        st.blocks = 0;
         st.limit = limit;
         st.sw_age = 0;
         s.seed[j] = st;
@@ -1350,6 +1351,7 @@ __global__ void __launch_bounds__(WG) k_block_finalize(SolveDev s)
         // the deferred update read the block's residual history once per row
         if (st.step > 0)
             atomicAdd(&s.stats[0], (unsigned long long)st.step * 16ull * (unsigned long long)s.desc[j].n);
+        if (st.status != SEED_STOPPED) w.blocks = st.blocks + 1;
         w.base = (st.base + st.step) % s.R;
         w.step = 0;
         w.n_active = n_active;
@@ -1783,7 +1785,8 @@ __global__ void k_all_stopped(const SeedState *__restrict__ seed, int64_t K, int
 }
 
 // Per-pair reports in the C ABI's layout, the worst status (2 breakdown, 1 not converged) and,
-// from the first workgroup, the seed iterations and switches summed over right-hand sides.
+// from the first workgroup, the seed iterations and switches summed over right-hand sides and the
+// blocks of the last one to stop.
 // worst and totals start at zero.
 __global__ void k_pack_report(int64_t K, int64_t M, int fixed, const int32_t *__restrict__ iters,
                               const int32_t *__restrict__ pstatus, const double *__restrict__ res,
@@ -1803,13 +1806,15 @@ __global__ void k_pack_report(int64_t K, int64_t M, int fixed, const int32_t *__
         if (code) atomicMax(worst, code);
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
-        long long it = 0, sw = 0;
+        long long it = 0, sw = 0, nb = 0;
         for (int64_t j = 0; j < K; ++j) {
             it += seed[j].iter;
             sw += seed[j].switches;
+            nb = max(nb, (long long)seed[j].blocks);
         }
         totals[0] = it;
         totals[1] = sw;
+        totals[2] = nb;
     }
 }
 

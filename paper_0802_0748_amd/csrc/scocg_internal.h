@@ -64,6 +64,7 @@ struct SeedState {
     int32_t n_active;    // pairs still active after the last block
     int32_t switches;    // number of seed switches so far
     int32_t limit;       // iteration limit (max_iter or fixed_iter)
+    int32_t blocks;      // blocks until it stopped
     int32_t sw_age;      // block ends since the switch decision (its vectors are switched at 1)
 };
 

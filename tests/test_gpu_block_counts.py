@@ -1,0 +1,29 @@
+"""The blocks that last_timing reports: those that were run, in whole rounds between two looks at the states,
+whichever form the iterations take and whichever entry point is called."""
+
+import numpy as np
+import pytest
+
+import paper_0802_0748_amd as S
+from workloads import simple_cubic
+
+pytestmark = pytest.mark.gpu
+
+
+# 512 rows: one launch a block; 4,913: three an iteration
+@pytest.mark.parametrize("L", [8, 17])
+@pytest.mark.parametrize("block,opts", [(48, dict(fixed_iter=48)), (48, dict(fixed_iter=230)), (24, dict(fixed_iter=60)),
+                                        (8, dict(fixed_iter=9)), (48, dict(tol=1e-8, max_iter=3000)),
+                                        (32, dict(tol=1e-8, max_iter=3000))])
+def test_both_entry_points_count_the_same_blocks(L, block, opts):
+    H = S.Hamiltonian.from_csr(simple_cubic(L, np.random.default_rng(L).uniform(-1, 1, L ** 3)))
+    z = np.linspace(-4, 4, 5) + 0.3j
+    blocks = []
+    for entry in (S.greens_diag, S.greens_diag_noalloc):
+        entry(H, z, [0, 100], block=block, **opts)
+        blocks.append(S.last_timing()["blocks"])
+    assert blocks[0] == blocks[1]
+    if "fixed_iter" in opts:
+        looks = max(1, 64 // block)
+        done = -(-opts["fixed_iter"] // block)
+        assert blocks[0] == -(-done // looks) * looks
