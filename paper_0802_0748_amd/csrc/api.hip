@@ -1172,7 +1172,8 @@ int solve(SolveRequest &rq, hipStream_t st)
     bool done = false;
     // A block of five launches is too short to wait for the host's look at the states after each:
     // the next round is launched first (a round too many costs its empty launches, about 15 us).
-    const bool ahead = s.seed_block != 0;
+    // Not while the update's launches are timed: the empty ones would count among them.
+    const bool ahead = s.seed_block != 0 && !g_profiling;
     int64_t rounds = 0;
     hipEvent_t evST[2] = {};
     if (ahead)

@@ -27,3 +27,19 @@ def test_both_entry_points_count_the_same_blocks(L, block, opts):
         looks = max(1, 64 // block)
         done = -(-opts["fixed_iter"] // block)
         assert blocks[0] == -(-done // looks) * looks
+
+
+@pytest.mark.parametrize("schedule", ["serial", "overlap"])
+@pytest.mark.parametrize("L,block", [(8, 48), (8, 8), (17, 48)])
+def test_profiling_times_one_update_per_block(L, block, schedule):
+    H = S.Hamiltonian.from_csr(simple_cubic(L, np.random.default_rng(L).uniform(-1, 1, L ** 3)))
+    z = np.linspace(-4, 4, 5) + 0.3j
+    S.set_profiling(True)
+    try:
+        G = S.greens_diag(H, z, [0, 100], block=block, schedule=schedule, tol=1e-8, max_iter=3000)[0]
+        t = S.last_timing()
+    finally:
+        S.set_profiling(False)
+    assert t["update_launches"] == t["blocks"] > 0
+    G2 = S.greens_diag(H, z, [0, 100], block=block, schedule=schedule, tol=1e-8, max_iter=3000)[0]
+    assert S.last_timing()["blocks"] == t["blocks"] and np.array_equal(G.cpu().numpy(), G2.cpu().numpy())
