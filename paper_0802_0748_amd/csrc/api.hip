@@ -1222,7 +1222,9 @@ int solve(SolveRequest &rq, hipStream_t st)
         done = true;
         for (int64_t j = 0; j < K; ++j)
             if (now[j].status != SEED_STOPPED) done = false;
-        if (blocks > max_blocks) return fail(SCOCG_EHIP, "iteration driver did not terminate");
+        // (blocks launched ahead have not been looked at)
+        if (!done && blocks - (ahead ? per_sync : 0) > max_blocks)
+            return fail(SCOCG_EHIP, "iteration driver did not terminate");
     }
     if (ahead) {
         // the last round found every rhs stopped and changed nothing
