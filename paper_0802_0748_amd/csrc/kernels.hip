@@ -8,9 +8,9 @@
 //   per-shift vectors x_k, u_k                                : pair-major, FP64 or FP32 complex
 //   H : 64-row slices, each slice stored column-slot-major (slot k of the 64 rows is
 //       contiguous), FP64 values
-// All reductions are fixed-order: every workgroup writes a partial and one workgroup sums
-// the partials in index order, so results do not depend on scheduling and a rhs gives the
-// same bits whether it is solved alone or in a batch.
+// All reductions are fixed-order: every tile of rows gives a partial, and the partials are added in
+// one tree over their indices, by one workgroup or by each wave that needs the sum, so results do
+// not depend on scheduling and a rhs gives the same bits whether it is solved alone or in a batch.
 #include "device_common.h"
 #include "hubbard_rows.h"
 
@@ -392,15 +392,17 @@ __device__ inline void fold_commit(const SolveDev &s, int t, int64_t j)
 }
 
 // ---------------------------------------------------------------------------------------
-// One seed iteration is five launches, none of which needs a grid-wide fence (kernel
+// Matrices that one workgroup streams fast enough run a whole block in one launch (seed_block.hip).
+// Otherwise one seed iteration is five launches, none of which needs a grid-wide fence (kernel
 // boundaries order them):
 //   k_pupd    p_n = r_n + beta_{n-1} p_{n-1}                      (elementwise, in place)
 //   k_spmv    q = (z_s 1 - H) p_n;  partial sums of p_n.q         (RB right-hand sides per thread)
 //   k_alpha   alpha_n = rho_n / (p_n.q)                           (one workgroup per rhs)
 //   k_rupd    r_{n+1} = r_n - alpha_n q;  partial sums of r.r and |r|^2
 //   k_beta    rho_{n+1}, ||r_{n+1}||, beta_n, convergence of the seed (one workgroup per rhs)
-// With stored matrices of at most FOLD_TILES tiles (and FOLD_MAX_ITEMS in all) it is three: k_rupd works out alpha_n itself, and
-// k_pupd of the next iteration beta_n (FOLD; the block's last iteration has both launches).
+// With stored matrices of at most FOLD_TILES tiles (and FOLD_MAX_ITEMS in all) it is three: k_rupd works
+// out alpha_n itself, and k_pupd of the next iteration beta_n (FOLD; the block's last iteration has
+// both launches).
 // ---------------------------------------------------------------------------------------
 // k_pupd and k_rupd: one wave per 256-row tile, four rows per lane, so that a tile's sums need no LDS and
 // no barrier, four times the loads are in flight per wave, and a folded sum is worked out once per 256
@@ -1909,8 +1911,9 @@ hipError_t launch_block_iterations(const SolveDev &s, hipStream_t st)
     // or a few of a lattice of 5,000 to 65,536 rows: 1.15 to 1.25 times faster per call, 16 x 6 right-hand
     // sides in a batch (about 6,800 tiles) 221 -> 206 ms, 128 of 16,384 rows (8,192 tiles) 354 -> 345 ms.
     // With 256 of them (16,384 tiles) the sums that every wave repeats cost more than the launches: 13.84
-    // against 13.67 s per solve with the launches.  Beyond 256 tiles of one right-hand side one wave's four loads are not
-    // enough, and the launches are long against the gaps.
+    // against 13.67 s per solve with the launches; between 8,192 and 16,384 nothing was measured, so the
+    // line is the larger of the two that gained.  Beyond 256 tiles of one right-hand side one wave's four
+    // loads are not enough, and the launches are long against the gaps.
     const int64_t tiles = s.it_rhs ? s.n_it_rhs : s.K * s.nblk;
     const bool fold = !s.has_hub && s.n <= FOLD_TILES * WG && tiles <= FOLD_MAX_ITEMS;
     for (int t = 0; t < s.TB; ++t) {

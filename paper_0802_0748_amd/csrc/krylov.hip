@@ -467,9 +467,8 @@ __global__ void __launch_bounds__(WG) k_lz_alpha(LzDev s, int n)
 }
 
 // w <- w - a_n K_n and the partials of ||w||^2.  FOLD: a_n (see k_lz_alpha) from the tiles' sums by every
-// workgroup.  Groups and tiles are taken in the opposite order of k_lz_matvec, so that each kernel
-// starts on what the one before left in the caches.  Bound by memory, two vectors read and one
-// written: 17.5 us for 100 MB at the sizes above (5.7 TB/s).
+// workgroup.  Bound by memory, two vectors read and one written: 17.5 us for 100 MB at the sizes above
+// (5.7 TB/s).
 template <int RB, bool FOLD>
 __global__ void __launch_bounds__(WG) k_lz_axpy(LzDev s, int n)
 {

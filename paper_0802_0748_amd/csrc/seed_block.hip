@@ -27,8 +27,11 @@ __device__ inline void unroll(F &&f)
 // phases become workgroup barriers that wait on LDS only.
 //
 // What bounds it: up to 1024 rows the chain of one iteration (gathers, two sums over the rows,
-// two complex divisions, three to seven barriers); above, the gathers from LDS and, where the
-// matrix does not fit in registers, its stream through L2, once per iteration and workgroup.
+// two complex divisions, three to seven barriers); above, where the matrix does not fit in
+// registers, that chain and the latency of its slots, one chunk of which is in flight per wave: with
+// 4096 rows of 7 entries (8.5 us an iteration) the waves wait for 56 % of their cycles, the LDS is
+// busy for 23 %, the vector units issue for 47 %, and the matrix comes at 40 GB/s; each further
+// slot costs 0.148 ns (81 GB/s), so wide rows are left to the launches (seed_block_pays).
 // Measured per iteration, five launches against this: 200 rows of up to 17 entries 20 -> 1.7 us,
 // 512 rows (cubic 8^3) 20 -> 2.3 us, 4096 rows (cubic 16^3) 16.2 -> 8.5 us for one right-hand side
 // and 36 -> 12 us for 300.
@@ -42,7 +45,9 @@ __device__ inline void unroll(F &&f)
 //
 // NPAD: rows the instance has room for (256 ... 8192).  W: matrix slots per row a lane keeps in
 // registers for the whole block (rows of up to W entries; columns as 16-bit pairs), or 0: the
-// slots are read each iteration, the next ones in flight while the last are added.
+// slots are read each iteration, the next ones in flight while the last are added.  (Two instances
+// spill: <8192, 0> 60 vector registers, 236 bytes of scratch a lane, and <2048, 0> four; the
+// first is ahead of the launches all the same, 4.6 against 5.4 ms, see seed_block_holds.)
 // ---------------------------------------------------------------------------------------
 __device__ inline void lds_barrier()
 {
