@@ -983,7 +983,8 @@ int solve(SolveRequest &rq, hipStream_t st)
     ALLOC(bp1, K * s.nblk * sizeof(double));
     // what the report copies to the host in one piece (residuals, statistics, iterations, statuses,
     // switch log), then the small arrays that start at zero with it
-    const size_t o_stats = KM * sizeof(double), o_iters = o_stats + 4 * sizeof(unsigned long long);
+    const size_t stat_groups = (size_t)(K * pair_groups(K, M));
+    const size_t o_stats = KM * sizeof(double), o_iters = o_stats + 2 * stat_groups * sizeof(unsigned long long);
     const size_t o_pst = o_iters + KM * sizeof(int32_t), o_swlog = o_pst + KM * sizeof(int32_t);
     const size_t rep_bytes = o_swlog + 2 * KM * sizeof(int32_t);
     const size_t o_nact = rep_bytes, o_blk = o_nact + 2 * KM * sizeof(int32_t);
@@ -1275,8 +1276,13 @@ int solve(SolveRequest &rq, hipStream_t st)
     g_swlog.count.resize(K);
     g_swlog.log.assign(h_sw, h_sw + KM * 2);
     for (int64_t j = 0; j < K; ++j) g_swlog.count[j] = hs[j].switches;
-    g_timing.update_bytes = (double)h_stats[0];
-    g_timing.update_flops = (double)h_stats[2];
+    unsigned long long update_bytes = 0, update_flops = 0;
+    for (size_t g = 0; g < stat_groups; ++g) {
+        update_bytes += h_stats[2 * g];
+        update_flops += h_stats[2 * g + 1];
+    }
+    g_timing.update_bytes = (double)update_bytes;
+    g_timing.update_flops = (double)update_flops;
     float tot_ms = 0;
     HIPCHK(hipEventElapsedTime(&tot_ms, ev_t0, ev_t1));
     g_timing.total_ms = tot_ms;
@@ -1972,7 +1978,7 @@ extern "C" int greens_diag_noalloc(scocg_csr_t H, int64_t n_shift, const double 
         L.p1 = (double *)c.take((size_t)K * nblk * sizeof(double));
         L.cnt = (uint32_t *)c.take(K * sizeof(uint32_t));
         L.sd = (int32_t *)c.take(K * sizeof(int32_t));
-        L.stats = (unsigned long long *)c.take(3 * sizeof(unsigned long long));
+        L.stats = (unsigned long long *)c.take(2 * sizeof(unsigned long long));
         L.swlog = (int32_t *)c.take(KM * 2 * sizeof(int32_t));
         L.flag = (int32_t *)c.take(sizeof(int32_t));
         L.worst = (int32_t *)c.take(sizeof(int32_t));
@@ -2066,7 +2072,7 @@ extern "C" int greens_diag_noalloc(scocg_csr_t H, int64_t n_shift, const double 
     s.part2 = L.p2;
     s.part1 = L.p1;
     s.cnt = L.cnt;
-    s.stats = L.stats;
+    s.stats = (unsigned long long *)L.rep;  // (free until the report is packed: 24 bytes a pair)
     s.swlog = L.swlog;
     s.desc = L.desc;
 
@@ -2079,7 +2085,9 @@ extern "C" int greens_diag_noalloc(scocg_csr_t H, int64_t n_shift, const double 
     HIPCHK(launch_zero(L.cnt, K * sizeof(uint32_t), st));
     HIPCHK(launch_zero(L.nact, 2 * KM * sizeof(int32_t), st));
     HIPCHK(launch_zero(L.blk, 2 * (size_t)K * 4 * sizeof(int32_t), st));
-    HIPCHK(launch_zero(L.stats, 3 * sizeof(unsigned long long), st));
+    const int64_t stat_groups = K * pair_groups(K, M);
+    static_assert(sizeof(PairReportDev) >= 2 * sizeof(unsigned long long), "the statistics lie in the report");
+    HIPCHK(launch_zero(s.stats, 2 * (size_t)stat_groups * sizeof(unsigned long long), st));
     HIPCHK(launch_zero(L.swlog, KM * 2 * sizeof(int32_t), st));
     HIPCHK(launch_zero(L.worst, sizeof(int32_t), st));
     HIPCHK(launch_zero(L.totals, 3 * sizeof(long long), st));
@@ -2118,10 +2126,11 @@ extern "C" int greens_diag_noalloc(scocg_csr_t H, int64_t n_shift, const double 
         if (blocks > max_blocks) return fail(SCOCG_EHIP, "iteration driver did not terminate");
     }
     HIPCHK(launch_gather_diag(s, L.idx, (double2 *)G, st));
+    HIPCHK(launch_sum_stats(s.stats, stat_groups, L.stats, st));
     HIPCHK(launch_pack_report(K, M, s.fixed, L.iters, L.pst, L.res, L.seed, L.rep, L.worst, L.totals, st));
     int32_t worst = 0;
     long long totals[3] = {0, 0, 0};
-    unsigned long long stats[3] = {0, 0, 0};
+    unsigned long long stats[2] = {0, 0};
     HIPCHK(hipMemcpyAsync(&worst, L.worst, sizeof(int32_t), hipMemcpyDeviceToHost, st));
     HIPCHK(hipMemcpyAsync(totals, L.totals, sizeof(totals), hipMemcpyDeviceToHost, st));
     HIPCHK(hipMemcpyAsync(stats, L.stats, sizeof(stats), hipMemcpyDeviceToHost, st));
@@ -2132,7 +2141,7 @@ extern "C" int greens_diag_noalloc(scocg_csr_t H, int64_t n_shift, const double 
     g_timing.switches = totals[1];
     g_timing.blocks = (std::max<int64_t>(totals[2], 1) + round - 1) / round * round;
     g_timing.update_bytes = (double)stats[0];
-    g_timing.update_flops = (double)stats[2];
+    g_timing.update_flops = (double)stats[1];
     if (worst == 2) return fail(SCOCG_EBREAKDOWN, "COCG breakdown on at least one pair");
     if (worst == 1) return fail(SCOCG_ENOCONV, "at least one pair did not converge");
     return SCOCG_OK;

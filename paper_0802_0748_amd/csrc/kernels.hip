@@ -1063,22 +1063,21 @@ __global__ void __launch_bounds__(NT) k_beta(SolveDev s)
 // lanes.  beta_{n-1} / alpha_{n-1} is the rhs's own and formed once per step, and pi_{n-1} / pi_n is
 // one step's quotient of the next.  One thread per pair, with the four divisions of a step in the
 // chain, took 55-65 us for any number of pairs up to a few thousand; this takes 7-9 us (P = 16),
-// P = 64 keeps the statistics' atomics few when there are tens of thousands of pairs.
+// P = 64 takes fewer workgroups when there are tens of thousands of pairs (65,536: 14 us a block of 4).
 // Roundings are written out (cmul_f, cdiv_f): those of the expressions above.
 // ---------------------------------------------------------------------------------------
 static constexpr int PS_STEPS = 48;  // longest block
 
 template <typename V, int P>
-__global__ void __launch_bounds__(P == 16 ? 256 : 512) k_pair_scalars(SolveDev s)
+__global__ void __launch_bounds__(P == 64 ? 512 : 16 * P) k_pair_scalars(SolveDev s)
 {
-    constexpr int NT = P == 16 ? 256 : 512;
+    constexpr int NT = P == 64 ? 512 : 16 * P;
     __shared__ double2 pin[PS_STEPS + 2][P + 1];  // pi_{n0-1}, pi_{n0}, pi_{n0+1} ... per pair
     __shared__ double2 ha[PS_STEPS], hb[PS_STEPS], hc[PS_STEPS], hs[PS_STEPS];
     __shared__ double hr[PS_STEPS];
     __shared__ int stop[P];  // first step that ends the pair: 2 t (pi = 0), 2 t + 1 (converged)
     __shared__ int live[P];
     __shared__ unsigned long long st_bytes, st_flops;
-    __shared__ unsigned int st_count;
     const int64_t j = blockIdx.y;
     const int64_t k0 = (int64_t)blockIdx.x * P;
     const int64_t p0 = j * s.M + k0;  // first pair
@@ -1122,7 +1121,6 @@ __global__ void __launch_bounds__(P == 16 ? 256 : 512) k_pair_scalars(SolveDev s
     if (tid == 0) {
         st_bytes = 0ull;
         st_flops = 0ull;
-        st_count = 0u;
     }
     __syncthreads();
     if (tid < npair && live[tid]) {
@@ -1194,15 +1192,15 @@ __global__ void __launch_bounds__(P == 16 ? 256 : 512) k_pair_scalars(SolveDev s
                 const unsigned long long n = (unsigned long long)s.desc[j].n;
                 atomicAdd(&st_bytes, nv * rw * esz * n);
                 atomicAdd(&st_flops, (unsigned long long)na * 8ull * nv * n);
-                atomicAdd(&st_count, 1u);
             }
         }
     }
     __syncthreads();
-    if (tid == 0 && st_count > 0) {
-        atomicAdd(&s.stats[0], st_bytes);
-        atomicAdd(&s.stats[1], (unsigned long long)st_count);
-        atomicAdd(&s.stats[2], st_flops);
+    if (tid == 0 && st_bytes > 0) {
+        // (an addition that nothing waits for; no other workgroup adds here at the same time)
+        unsigned long long *stats = s.stats + 2 * (j * gridDim.x + blockIdx.x);
+        atomicAdd(&stats[0], st_bytes);
+        atomicAdd(&stats[1], st_flops);
     }
     if (tid >= npair || !live[tid]) return;
     const int64_t pair = p0 + tid;
@@ -1276,7 +1274,7 @@ __global__ void __launch_bounds__(P == 16 ? 256 : 512) k_pair_scalars(SolveDev s
 // pi_k <- pi_k / pi_t, pi_{k,prev} <- pi_{k,prev} / pi_{t,prev}, alpha_prev <- alpha^t_n,
 // beta_prev <- beta^t_n, z_s <- z_t.
 // ---------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(WG) k_block_finalize(SolveDev s)
+__global__ void __launch_bounds__(WG) k_block_finalize(SolveDev s, int64_t stat_groups)
 {
     __shared__ int sh_cnt[WG];
     __shared__ int sh_brk[WG];
@@ -1352,7 +1350,7 @@ __global__ void __launch_bounds__(WG) k_block_finalize(SolveDev s)
         }
         // the deferred update read the block's residual history once per row
         if (st.step > 0)
-            atomicAdd(&s.stats[0], (unsigned long long)st.step * 16ull * (unsigned long long)s.desc[j].n);
+            atomicAdd(&s.stats[2 * j * stat_groups], (unsigned long long)st.step * 16ull * (unsigned long long)s.desc[j].n);
         if (st.status != SEED_STOPPED) w.blocks = st.blocks + 1;
         w.base = (st.base + st.step) % s.R;
         w.step = 0;
@@ -1827,6 +1825,35 @@ hipError_t launch_fill_desc(const RhsDesc &proto, int64_t K, int32_t seed, RhsDe
     return hipGetLastError();
 }
 
+// stats summed over the workgroups of k_pair_scalars
+__global__ void __launch_bounds__(WG) k_sum_stats(const unsigned long long *__restrict__ stats, int64_t groups,
+                                                  unsigned long long *__restrict__ out)
+{
+    __shared__ unsigned long long sh[2][WG];
+    unsigned long long a = 0, b = 0;
+    for (int64_t g = threadIdx.x; g < groups; g += WG) {
+        a += stats[2 * g];
+        b += stats[2 * g + 1];
+    }
+    sh[0][threadIdx.x] = a;
+    sh[1][threadIdx.x] = b;
+    __syncthreads();
+    for (int h = WG / 2; h > 0; h >>= 1) {
+        if ((int)threadIdx.x < h) {
+            sh[0][threadIdx.x] += sh[0][threadIdx.x + h];
+            sh[1][threadIdx.x] += sh[1][threadIdx.x + h];
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x < 2) out[threadIdx.x] = sh[threadIdx.x][0];
+}
+
+hipError_t launch_sum_stats(const unsigned long long *stats, int64_t groups, unsigned long long *out, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_sum_stats, dim3(1), dim3(WG), 0, st, stats, groups, out);
+    return hipGetLastError();
+}
+
 hipError_t launch_all_stopped(const SeedState *seed, int64_t K, int32_t *flag, hipStream_t st)
 {
     hipLaunchKernelGGL(k_all_stopped, dim3(1), dim3(WG), 0, st, seed, K, flag);
@@ -1923,24 +1950,43 @@ hipError_t launch_block_iterations(const SolveDev &s, hipStream_t st)
     return hipSuccess;
 }
 
+// Shifts per workgroup of k_pair_scalars (16 threads each, 8 of them at 64): 4 or 16 where a right-hand side has
+// no more (20,000 right-hand sides of one shift, blocks of 4 iterations: 30 us with 4, 64 with 16, 167
+// with 64, whose 52 KB of LDS let three workgroups on a compute unit; 3,000 of 5: 13 with 16, 28 with
+// 64), and 64 from where 16 would fill the chip several times over.
+static int pair_width(int64_t K, int64_t M)
+{
+    if (M <= 16) return M <= 4 ? 4 : 16;
+    return K * ((M + 15) / 16) > 1024 ? 64 : 16;
+}
+
+int64_t pair_groups(int64_t K, int64_t M)
+{
+    const int P = pair_width(K, M);
+    return (M + P - 1) / P;
+}
+
+template <typename V>
+static void launch_pair_scalars_as(const SolveDev &s, hipStream_t st)
+{
+    const dim3 g = grid2(pair_groups(s.K, s.M), s.K);
+    switch (pair_width(s.K, s.M)) {
+        case 4: hipLaunchKernelGGL((k_pair_scalars<V, 4>), g, dim3(64), 0, st, s); break;
+        case 16: hipLaunchKernelGGL((k_pair_scalars<V, 16>), g, dim3(256), 0, st, s); break;
+        default: hipLaunchKernelGGL((k_pair_scalars<V, 64>), g, dim3(512), 0, st, s);
+    }
+}
+
 hipError_t launch_pair_scalars(const SolveDev &s, hipStream_t st)
 {
-    // 16 shifts per workgroup until there are enough workgroups for the chip several times over
-    const bool wide = s.K * ((s.M + 15) / 16) > 1024;
-    const dim3 g = grid2((s.M + (wide ? 63 : 15)) / (wide ? 64 : 16), s.K);
-    if (wide) {
-        if (s.precision == 0) hipLaunchKernelGGL((k_pair_scalars<double2, 64>), g, dim3(512), 0, st, s);
-        else hipLaunchKernelGGL((k_pair_scalars<float2, 64>), g, dim3(512), 0, st, s);
-    } else {
-        if (s.precision == 0) hipLaunchKernelGGL((k_pair_scalars<double2, 16>), g, dim3(256), 0, st, s);
-        else hipLaunchKernelGGL((k_pair_scalars<float2, 16>), g, dim3(256), 0, st, s);
-    }
+    if (s.precision == 0) launch_pair_scalars_as<double2>(s, st);
+    else launch_pair_scalars_as<float2>(s, st);
     return hipGetLastError();
 }
 
 hipError_t launch_block_finalize(const SolveDev &s, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_block_finalize, dim3((unsigned)s.K), dim3(WG), 0, st, s);
+    hipLaunchKernelGGL(k_block_finalize, dim3((unsigned)s.K), dim3(WG), 0, st, s, pair_groups(s.K, s.M));
     return hipGetLastError();
 }
 

@@ -233,8 +233,9 @@ struct SolveDev {
     int has_red_small, has_red_big; // some rhs below / at or above 2^21 rows (per-rhs reduction width)
     int64_t hub_du_max;        // largest number of up-spin configurations among them
     int64_t hub_dd_max;        // largest down-spin block
-    unsigned long long *stats; // [0] algorithmic bytes of the deferred update, [1] updated pairs,
-                               // [2] its algorithmic flops
+    unsigned long long *stats; // [K * pair_groups][2] algorithmic bytes and flops of the deferred update, per
+                               // workgroup of k_pair_scalars (one address for all took 12 ns an addition:
+                               // 0.73 ms a block for 20,000 right-hand sides of one shift)
     // Work lists of batches whose right-hand sides have different row counts (null otherwise): a
     // launch then covers exactly the (group or rhs, row block) items that hold rows, instead of
     // the full rectangle of largest-row-count x right-hand sides with most workgroups exiting.
@@ -269,6 +270,10 @@ hipError_t launch_seed_block(const SolveDev &s, hipStream_t st);
 // the block's TB seed iterations, in whichever form s asks for
 hipError_t launch_block_iterations(const SolveDev &s, hipStream_t st);
 hipError_t launch_pair_scalars(const SolveDev &s, hipStream_t st);
+// workgroups of it per right-hand side
+int64_t pair_groups(int64_t K, int64_t M);
+// out[0], out[1] = the sums of stats
+hipError_t launch_sum_stats(const unsigned long long *stats, int64_t groups, unsigned long long *out, hipStream_t st);
 hipError_t launch_flush(const SolveDev &s, hipStream_t st);
 hipError_t launch_block_finalize(const SolveDev &s, hipStream_t st);
 hipError_t launch_switch_vectors(const SolveDev &s, hipStream_t st);

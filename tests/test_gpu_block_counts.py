@@ -43,3 +43,18 @@ def test_profiling_times_one_update_per_block(L, block, schedule):
     assert t["update_launches"] == t["blocks"] > 0
     G2 = S.greens_diag(H, z, [0, 100], block=block, schedule=schedule, tol=1e-8, max_iter=3000)[0]
     assert S.last_timing()["blocks"] == t["blocks"] and np.array_equal(G.cpu().numpy(), G2.cpu().numpy())
+
+
+@pytest.mark.parametrize("K,M", [(40, 3), (30, 16), (20, 50), (300, 70)])
+def test_update_counts_of_many_right_hand_sides_are_those_of_each(K, M):
+    H = S.Hamiltonian.from_csr(simple_cubic(6, np.random.default_rng(M).uniform(-1, 1, 216)))
+    z = np.linspace(-4, 4, M) + 0.3j
+    idx = [(7 * j) % 216 for j in range(K)]
+
+    def counts(rhs, entry=S.greens_diag):
+        entry(H, z, rhs, block=8, tol=1e-8, max_iter=300)
+        return [S.last_timing()[k] for k in ("update_bytes", "update_flops")]
+
+    want = np.sum([counts([j]) for j in sorted(set(idx)) for _ in range(idx.count(j))], axis=0)
+    for entry in (S.greens_diag, S.greens_diag_noalloc):
+        assert np.array_equal(counts(idx, entry), want)

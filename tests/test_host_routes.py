@@ -107,3 +107,13 @@ for K, M in ((3, 5), (3000, 64), (65535, 2), (2, 70000)):
     x = [fake.fake_threads_x(i) for i in range(fake.fake_launches()) if b'k_pair_scalars' in fake.fake_name(i)]
     assert x and max(x) <= 16 * (M + 63), (K, M, max(x))
 """, tmp_path)
+
+
+@pytest.mark.parametrize("K,M,threads", [(20000, 1, 64), (3000, 4, 64), (3000, 16, 256), (2, 70, 5 * 256), (400, 70, 2 * 512)])
+def test_shift_scalars_take_no_more_threads_than_the_shifts_of_a_right_hand_side_need(K, M, threads, tmp_path):
+    run(f"""
+_, H = upload(*band(64, 3))
+greens(H, {K}, {M}, block=4)
+x = [fake.fake_threads_x(i) for i in range(fake.fake_launches()) if b'k_pair_scalars' in fake.fake_name(i)]
+assert x and set(x) == {{{threads}}}, set(x)
+""", tmp_path)
