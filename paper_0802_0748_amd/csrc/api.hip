@@ -875,10 +875,11 @@ int solve(SolveRequest &rq, hipStream_t st)
     for (int64_t j = 0; j < K; ++j) (hdesc[j].hub ? s.has_hub : s.has_sell) = 1;
     for (int64_t j = 0; j < K; ++j) (hdesc[j].n >= RED_BIG_ROWS ? s.has_red_big : s.has_red_small) = 1;
     s.seed_block = !s.has_hub && seed_block_holds(n, K);
+    const int layout = seed_block_layout(n);
     for (int64_t j = 0; j < K; ++j) {
         const DevCSR &dj = (rq.Hj.empty() ? rq.H : rq.Hj[j])->d;
         s.max_w = std::max(s.max_w, dj.max_w);
-        s.seed_block = s.seed_block && seed_block_pays(dj.n, K, dj.ell_nnz, dj.max_w, dj.chain[seed_block_layout(n)]);
+        s.seed_block = s.seed_block && seed_block_pays(dj.n, K, dj.ell_nnz, dj.max_w, dj.chain[layout], layout);
     }
     s.hub_lds = 1;
     for (int64_t j = 0; j < K; ++j) {
@@ -2032,8 +2033,9 @@ extern "C" int greens_diag_noalloc(scocg_csr_t H, int64_t n_shift, const double 
     (d.d_hub ? s.has_hub : s.has_sell) = 1;
     (n >= RED_BIG_ROWS ? s.has_red_big : s.has_red_small) = 1;
     s.max_w = d.max_w;
+    const int layout = seed_block_layout(n);
     s.seed_block = !s.has_hub && seed_block_holds(n, K) &&
-                   seed_block_pays(n, K, d.ell_nnz, d.max_w, d.chain[seed_block_layout(n)]);
+                   seed_block_pays(n, K, d.ell_nnz, d.max_w, d.chain[layout], layout);
     s.hub_lds = 1;
     if (d.d_hub) {
         if (d.hub_Dd > HUB_LDS_MAX || n / d.hub_Dd > (n + 255) / 256) s.hub_lds = 0;

@@ -106,24 +106,31 @@ inline bool seed_block_holds(int64_t n, int64_t K)
 {
     return n <= SEED_BLOCK_ROWS || (n <= SEED_BLOCK_ROWS_MANY && K >= SEED_BLOCK_RHS);
 }
-// A workgroup streams its matrix every iteration: 0.148 ns a stored slot, or, where the slots are uneven,
-// the longest chain of one wave (its slices' widths, one after the other), a step of it 500 slots'
-// time.  The launches spread the slots over the chip: their time is that of 440 slots per entry of the
-// widest row, of 810 per entry of the mean row for two right-hand sides and more (two share a
-// thread), or, once the chip is full, of slots * K / 154; and they cost about 9 us more per iteration,
-// 60,000 slots.  us per iteration, one launch against three: 4096 rows of 9 entries 12 / 16, of 17
-// 17.3 / 16.5, of 65 45 / 20, of 257 163 / 33; 256 of them of 200 entries 78 / 31; one of them dense
-// 305 / 215; for 16 right-hand sides 17 entries 18 / 22, 33 27 / 24; for 256 65 entries 57 / 97; 2048
-// rows of 33 entries 17.7 / 17.5; 1024 rows of 65 entries 15.7 / 19.4, of 257 45 / 32.
-inline bool seed_block_pays(int64_t n, int64_t K, int64_t slots, int64_t max_w, int64_t chain)
-{
-    const int64_t one = std::max(slots, 500 * chain);
-    const int64_t chip = std::max(std::max(440 * max_w, K > 1 ? 810 * slots / n : 0), slots * K / 154);
-    return one - chip <= 60000;
-}
 // The slices of a wave when the longest right-hand side of the call has n rows: 0 to 3 for one slice, two
 // (every other one of a 256-row tile), a tile, two tiles (t and t + 16).
 inline int seed_block_layout(int64_t n) { return n <= 1024 ? 0 : n <= 2048 ? 1 : n <= SEED_BLOCK_ROWS ? 2 : 3; }
+// A workgroup streams its matrix every iteration: 0.148 ns a stored slot (0.2 beyond 4096 rows, where
+// registers spill), or, where the slots are uneven, the longest chain of one wave (its slices' widths,
+// one after the other), a step of it 500 slots' time; more right-hand sides than the chip holds
+// workgroups (one per compute unit, two up to 512 rows) take it in rounds.  The launches spread the
+// slots over the chip: their time is that of 440 slots per entry of the widest row, of 810 per entry
+// of the mean row for two right-hand sides and more (two share a thread), or, once the chip is full,
+// of slots * K / 154; and they cost 9 us more per iteration (15 beyond 4096 rows), 60,000 slots.  us
+// per iteration, one launch against three: 4096 rows of 9 entries 12 / 16, of 17 17.3 / 16.5, of 65
+// 45 / 20, of 257 163 / 33; 256 of them of 200 entries 78 / 31; one of them dense 305 / 215; for 16
+// right-hand sides 17 entries 18 / 22, 33 27 / 24; for 256 65 entries 83 / 116, for 260 127 / 121; 2048
+// rows of 33 entries 17.7 / 17.5; 1024 rows of 65 entries 15.7 / 19.4, of 257 45 / 32; 6000 rows of 17
+// entries, 128 right-hand sides 48 / 55, 260 of them 114 / 100.  (Over 267 sizes the choice costs 0.4 %
+// on average against the better form, 14 % at most, and none is slower than five launches were.)
+inline bool seed_block_pays(int64_t n, int64_t K, int64_t slots, int64_t max_w, int64_t chain, int layout)
+{
+    const int64_t resident = n <= 512 && layout == 0 ? 512 : 256, rounds = (K + resident - 1) / resident;
+    int64_t one = std::max(slots, 500 * chain);
+    if (layout == 3) one = one * 7 / 5;
+    one = rounds * one + (rounds - 1) * 5 * n;
+    const int64_t chip = std::max(std::max(440 * max_w, K > 1 ? 810 * slots / n : 0), slots * K / 154);
+    return one - chip <= (layout == 3 ? 100000 : 60000);
+}
 
 // Right-hand sides of at least this many rows sum their seed reductions with 1024 threads.
 static constexpr int64_t RED_BIG_ROWS = 1 << 21;

@@ -58,8 +58,11 @@ def uneven(n, heavy, width):
     # uneven rows: a wave's chain of slots is longer than the mean
     ("1, uneven(4096, 64, 200)", True), ("1, uneven(4096, 256, 200)", False), ("1, uneven(2048, 256, 400)", False),
     # until there are enough right-hand sides for the whole chip
-    ("256, band(4096, 257)", True), ("128, band(6000, 33)", True), ("128, band(6000, 129)", False),
+    ("256, band(4096, 257)", True), ("128, band(6000, 17)", True), ("128, band(6000, 129)", False),
     ("127, band(6000, 7)", False),
+    # ... and not for a few more than one round of workgroups
+    ("260, band(4096, 65)", False), ("512, band(4096, 65)", True), ("260, band(6000, 17)", False), ("256, band(6000, 17)", True),
+    ("260, band(4096, 7)", True), ("400, band(512, 511)", True),
     # one wide matrix of a batch is enough
     ("2, band(300, 7), band(4000, 129)", False), ("2, band(300, 7), band(4000, 7)", True)])
 def test_one_launch_iterations_only_where_one_workgroup_streams_as_fast(what, one, tmp_path):
