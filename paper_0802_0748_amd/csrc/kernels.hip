@@ -1350,7 +1350,8 @@ __global__ void __launch_bounds__(WG) k_block_finalize(SolveDev s, int64_t stat_
         }
         // the deferred update read the block's residual history once per row
         if (st.step > 0)
-            atomicAdd(&s.stats[2 * j * stat_groups], (unsigned long long)st.step * 16ull * (unsigned long long)s.desc[j].n);
+            atomicAdd(&s.stats[2 * j * stat_groups],
+                      (unsigned long long)st.step * 16ull * (unsigned long long)s.desc[j].n);
         if (st.status != SEED_STOPPED) w.blocks = st.blocks + 1;
         w.base = (st.base + st.step) % s.R;
         w.step = 0;
