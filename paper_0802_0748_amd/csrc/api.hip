@@ -64,12 +64,12 @@ static bool device_ok(const void *p)
 // Work buffers of 1 to 256 MiB are kept when a call ends and handed to the next one that asks for
 // about their size: freeing and allocating them again took 1.3 of the 3.1 ms of a 128-row energy
 // with gradient (hipFree 1.0 ms, hipMalloc 0.3 ms; smaller blocks cost half a microsecond).  Larger
-// blocks are allocated on each call, which bounds what an idle library holds (a call with 1.2 GB of them
-// took 9 ms, and 35 once the calls had allocated as much as the card holds, it seems because memory
-// is then cleared before it is handed out again).  At most KEEP_BYTES stay, the oldest go first; all go when the last matrix (or tape) is released, an
-// allocation fails, or the caller asks (scocg_release_workspace).  A block comes back only after the
-// stream of its call has drained, so whoever takes it next, on any thread or stream, finds it idle;
-// contents are never relied on.
+// blocks are allocated on each call, which bounds what an idle library holds (a call with 1.2 GB of
+// them took 9 ms, and 35 once the calls had allocated as much as the card holds, it seems because
+// memory is then cleared before it is handed out again).  At most KEEP_BYTES stay, the oldest go
+// first; all go when the last matrix (or tape) is released, an allocation fails, or the caller asks
+// (scocg_release_workspace).  A block comes back only after the stream of its call has drained, so
+// whoever takes it next, on any thread or stream, finds it idle; contents are never relied on.
 class Keeper {
 public:
     static constexpr size_t KEEP_MIN = 1ull << 20, KEEP_MAX = 256ull << 20, KEEP_BYTES = 1ull << 30;
