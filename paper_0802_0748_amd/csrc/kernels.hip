@@ -781,11 +781,14 @@ static constexpr int SPMV_TAIL = 4;
 // the column and value of each slot are loaded once and serve all RB gathers.  The products
 // are summed in slot order in every configuration, so a rhs gets the same bits alone or in
 // a batch.
+// FOLD: the state is brought up to date here (see fold_beta), by an instance of its own: with a store to
+// it in the kernel the compiler keeps the state and the descriptors in vector registers (76 instead of 66
+// with two right-hand sides, 102 instead of 95 us at 256 of 16,384 rows beside the update).
 // HUB: the instance for right-hand sides with a matrix-free Hubbard operator (a separate
 // kernel, so the stored-matrix instance keeps its small register footprint); each instance
 // leaves the other kind's right-hand sides alone.
-template <int RB, bool HUB>
-__global__ void __launch_bounds__(WG) k_spmv(SolveDev s, int fold_t)
+template <int RB, bool HUB, bool FOLD = false>
+__global__ void __launch_bounds__(WG) k_spmv(SolveDev s, int t)
 {
     __shared__ double2 sh2[WG];
     __shared__ double2 sh2b[RB > 1 ? WG : 1];
@@ -809,11 +812,11 @@ __global__ void __launch_bounds__(WG) k_spmv(SolveDev s, int fold_t)
             const SeedState *st = s.seed + j0 + b;
             zs[b] = st->zs;
             // (folded: the state is being brought up to date, see below)
-            run[b] = fold_t ? s.rnhist[(j0 + b) * s.TB + fold_t] == GO_RUN : st->status == SEED_RUNNING && st->step < s.TB;
+            run[b] = FOLD ? s.rnhist[(j0 + b) * s.TB + t] == GO_RUN : st->status == SEED_RUNNING && st->step < s.TB;
         }
         any |= run[b];
     }
-    if (!HUB && fold_t && rb == 0 && threadIdx.x < RB && j0 + threadIdx.x < s.K) fold_commit(s, fold_t, j0 + threadIdx.x);
+    if (FOLD && rb == 0 && threadIdx.x < RB && j0 + threadIdx.x < s.K) fold_commit(s, t, j0 + threadIdx.x);
     if (!any) return;
     const RhsDesc d = s.desc[j0];
     if ((d.hub != nullptr) != HUB) return;
@@ -1893,8 +1896,8 @@ static hipError_t launch_seed_iteration(const SolveDev &s, int t, bool fold, hip
     const int RB = s.spmv_rb;
     const int64_t G = (s.K + RB - 1) / RB;
     const dim3 gp = s.it_grp ? dim3((unsigned)s.n_it_grp) : grid2(s.nblk, G);
-    const int fold_t = fold ? t : 0;
-    if (fold_t) {
+    const bool folded = fold && t > 0;  // (the block's first iteration begins with a state that is up to date)
+    if (folded) {
         if (RB == 2) hipLaunchKernelGGL((k_pupd<2, true>), gp, dim3(64), 0, st, s, t);
         else hipLaunchKernelGGL((k_pupd<1, true>), gp, dim3(64), 0, st, s, t);
     } else {
@@ -1903,8 +1906,11 @@ static hipError_t launch_seed_iteration(const SolveDev &s, int t, bool fold, hip
     }
     const int64_t nwg = s.it_grp ? s.n_it_grp : (G < 8 ? s.nblk * G : s.nblk * 8 * ((G + 7) / 8));
     if (s.has_sell) {
-        if (RB == 2) hipLaunchKernelGGL((k_spmv<2, false>), dim3((unsigned)nwg), dim3(WG), 0, st, s, fold_t);
-        else hipLaunchKernelGGL((k_spmv<1, false>), dim3((unsigned)nwg), dim3(WG), 0, st, s, fold_t);
+        const dim3 gs((unsigned)nwg);
+        if (folded && RB == 2) hipLaunchKernelGGL((k_spmv<2, false, true>), gs, dim3(WG), 0, st, s, t);
+        else if (folded) hipLaunchKernelGGL((k_spmv<1, false, true>), gs, dim3(WG), 0, st, s, t);
+        else if (RB == 2) hipLaunchKernelGGL((k_spmv<2, false>), gs, dim3(WG), 0, st, s, t);
+        else hipLaunchKernelGGL((k_spmv<1, false>), gs, dim3(WG), 0, st, s, t);
     }
     if (s.has_hub) {
         if (s.hub_lds) {

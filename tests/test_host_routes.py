@@ -120,3 +120,18 @@ greens(H, {K}, {M}, block=4)
 x = [fake.fake_threads_x(i) for i in range(fake.fake_launches()) if b'k_pair_scalars' in fake.fake_name(i)]
 assert x and set(x) == {{{threads}}}, set(x)
 """, tmp_path)
+
+
+def test_products_of_iterations_that_are_not_folded_take_the_instance_without_the_state(tmp_path):
+    """The instance that brings the seed state up to date needs more registers: only the folded iterations
+    (from a block's second one on) take it."""
+    run("""
+for n, K, folded in ((5000, 3, True), (5000, 1, True), (66000, 3, False), (66000, 1, False), (33000, 64, False)):
+    _, H = upload(*band(n, 3))
+    fake.fake_forget()
+    assert greens(H, K, 1, block=4) == C.OK, lib.scocg_last_error()
+    rb = 2 if K > 1 else 1
+    plain, state = [launched(f'k_spmvILi{rb}ELb0ELb{f}E') for f in (0, 1)]
+    assert plain > 0 and state == (3 * plain if folded else 0), (n, K, plain, state)
+    lib.csr_free(H)
+""", tmp_path)
