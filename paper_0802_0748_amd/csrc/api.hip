@@ -985,7 +985,7 @@ int solve(SolveRequest &rq, hipStream_t st)
     ALLOC(bp1, K * s.nblk * sizeof(double));
     // what the report copies to the host in one piece (residuals, statistics, iterations, statuses,
     // switch log), then the small arrays that start at zero with it
-    const size_t stat_groups = (size_t)(K * pair_groups(K, M));
+    const size_t stat_groups = (size_t)(K * pair_groups(M));
     const size_t o_stats = KM * sizeof(double), o_iters = o_stats + 2 * stat_groups * sizeof(unsigned long long);
     const size_t o_pst = o_iters + KM * sizeof(int32_t), o_swlog = o_pst + KM * sizeof(int32_t);
     const size_t rep_bytes = o_swlog + 2 * KM * sizeof(int32_t);
@@ -2088,7 +2088,7 @@ extern "C" int greens_diag_noalloc(scocg_csr_t H, int64_t n_shift, const double 
     HIPCHK(launch_zero(L.cnt, K * sizeof(uint32_t), st));
     HIPCHK(launch_zero(L.nact, 2 * KM * sizeof(int32_t), st));
     HIPCHK(launch_zero(L.blk, 2 * (size_t)K * 4 * sizeof(int32_t), st));
-    const int64_t stat_groups = K * pair_groups(K, M);
+    const int64_t stat_groups = K * pair_groups(M);
     static_assert(sizeof(PairReportDev) >= 2 * sizeof(unsigned long long), "the statistics lie in the report");
     HIPCHK(launch_zero(s.stats, 2 * (size_t)stat_groups * sizeof(unsigned long long), st));
     HIPCHK(launch_zero(L.swlog, KM * 2 * sizeof(int32_t), st));

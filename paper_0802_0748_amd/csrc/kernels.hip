@@ -1059,22 +1059,23 @@ __global__ void __launch_bounds__(NT) k_beta(SolveDev s)
 // (two complex multiply-adds per step instead of three for p^k directly).  The kernel
 // writes (a'_n, b'_n) for every step of the block in which the pair is still active.
 //
-// A workgroup of 16 P threads takes P shifts of one rhs (a row of the grid).  Only the recurrence of pi is serial: P
-// lanes run it over the block (about five dependent operations a step, pi_n kept in LDS), and
-// everything that hangs off it (the residual and the stopping test, the quotients and (a'_n, b'_n))
-// is one item per pair and step over all threads, written with consecutive steps in consecutive
-// lanes.  beta_{n-1} / alpha_{n-1} is the rhs's own and formed once per step, and pi_{n-1} / pi_n is
-// one step's quotient of the next.  One thread per pair, with the four divisions of a step in the
-// chain, took 55-65 us for any number of pairs up to a few thousand; this takes 7-9 us (P = 16),
-// P = 64 takes fewer workgroups when there are tens of thousands of pairs (65,536: 14 us a block of 4).
+// A workgroup of 16 P threads takes P shifts of one rhs (a row of the grid).  Only the recurrence of
+// pi is serial: P lanes run it over the block (about five dependent operations a step, pi_n kept in
+// LDS), and everything that hangs off it (the residual and the stopping test, the quotients and
+// (a'_n, b'_n)) is one item per pair and step over all threads, written with consecutive steps in
+// consecutive lanes.  beta_{n-1} / alpha_{n-1} is the rhs's own and formed once per step, and
+// pi_{n-1} / pi_n is one step's quotient of the next.  One thread per pair, with the four divisions of a
+// step in the chain, took 55-65 us for any number of pairs up to a few thousand; this takes 7-9 us.
+// P = 16 (17 KB of LDS) or, for at most 4 shifts, 4: beside the deferred update of 256 rhs of 256 shifts, which
+// leaves 16 KB of a compute unit's LDS, 81 us a block (one thread per pair: 148; P = 64, with 56 KB: 996).
 // Roundings are written out (cmul_f, cdiv_f): those of the expressions above.
 // ---------------------------------------------------------------------------------------
 static constexpr int PS_STEPS = 48;  // longest block
 
 template <typename V, int P>
-__global__ void __launch_bounds__(P == 64 ? 512 : 16 * P) k_pair_scalars(SolveDev s)
+__global__ void __launch_bounds__(16 * P) k_pair_scalars(SolveDev s)
 {
-    constexpr int NT = P == 64 ? 512 : 16 * P;
+    constexpr int NT = 16 * P;
     __shared__ double2 pin[PS_STEPS + 2][P + 1];  // pi_{n0-1}, pi_{n0}, pi_{n0+1} ... per pair
     __shared__ double2 ha[PS_STEPS], hb[PS_STEPS], hc[PS_STEPS], hs[PS_STEPS];
     __shared__ double hr[PS_STEPS];
@@ -1957,31 +1958,18 @@ hipError_t launch_block_iterations(const SolveDev &s, hipStream_t st)
     return hipSuccess;
 }
 
-// Shifts per workgroup of k_pair_scalars (16 threads each, 8 of them at 64): 4 or 16 where a right-hand side has
-// no more (20,000 right-hand sides of one shift, blocks of 4 iterations: 30 us with 4, 64 with 16, 167
-// with 64, whose 52 KB of LDS let three workgroups on a compute unit; 3,000 of 5: 13 with 16, 28 with
-// 64), and 64 from where 16 would fill the chip several times over.
-static int pair_width(int64_t K, int64_t M)
-{
-    if (M <= 16) return M <= 4 ? 4 : 16;
-    return K * ((M + 15) / 16) > 1024 ? 64 : 16;
-}
+// Shifts per workgroup of k_pair_scalars: 16, or 4 where a right-hand side has no more (20,000 right-hand
+// sides of one shift, blocks of 4 iterations: 30 us with 4, 64 with 16).
+static int pair_width(int64_t M) { return M <= 4 ? 4 : 16; }
 
-int64_t pair_groups(int64_t K, int64_t M)
-{
-    const int P = pair_width(K, M);
-    return (M + P - 1) / P;
-}
+int64_t pair_groups(int64_t M) { return (M + pair_width(M) - 1) / pair_width(M); }
 
 template <typename V>
 static void launch_pair_scalars_as(const SolveDev &s, hipStream_t st)
 {
-    const dim3 g = grid2(pair_groups(s.K, s.M), s.K);
-    switch (pair_width(s.K, s.M)) {
-        case 4: hipLaunchKernelGGL((k_pair_scalars<V, 4>), g, dim3(64), 0, st, s); break;
-        case 16: hipLaunchKernelGGL((k_pair_scalars<V, 16>), g, dim3(256), 0, st, s); break;
-        default: hipLaunchKernelGGL((k_pair_scalars<V, 64>), g, dim3(512), 0, st, s);
-    }
+    const dim3 g = grid2(pair_groups(s.M), s.K);
+    if (pair_width(s.M) == 4) hipLaunchKernelGGL((k_pair_scalars<V, 4>), g, dim3(64), 0, st, s);
+    else hipLaunchKernelGGL((k_pair_scalars<V, 16>), g, dim3(256), 0, st, s);
 }
 
 hipError_t launch_pair_scalars(const SolveDev &s, hipStream_t st)
@@ -1993,7 +1981,7 @@ hipError_t launch_pair_scalars(const SolveDev &s, hipStream_t st)
 
 hipError_t launch_block_finalize(const SolveDev &s, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_block_finalize, dim3((unsigned)s.K), dim3(WG), 0, st, s, pair_groups(s.K, s.M));
+    hipLaunchKernelGGL(k_block_finalize, dim3((unsigned)s.K), dim3(WG), 0, st, s, pair_groups(s.M));
     return hipGetLastError();
 }
 

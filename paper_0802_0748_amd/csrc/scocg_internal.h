@@ -278,7 +278,7 @@ hipError_t launch_seed_block(const SolveDev &s, hipStream_t st);
 hipError_t launch_block_iterations(const SolveDev &s, hipStream_t st);
 hipError_t launch_pair_scalars(const SolveDev &s, hipStream_t st);
 // workgroups of it per right-hand side
-int64_t pair_groups(int64_t K, int64_t M);
+int64_t pair_groups(int64_t M);
 // out[0], out[1] = the sums of stats
 hipError_t launch_sum_stats(const unsigned long long *stats, int64_t groups, unsigned long long *out, hipStream_t st);
 hipError_t launch_flush(const SolveDev &s, hipStream_t st);

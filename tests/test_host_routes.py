@@ -112,7 +112,7 @@ for K, M in ((3, 5), (3000, 64), (65535, 2), (2, 70000)):
 """, tmp_path)
 
 
-@pytest.mark.parametrize("K,M,threads", [(20000, 1, 64), (3000, 4, 64), (3000, 16, 256), (2, 70, 5 * 256), (400, 70, 2 * 512)])
+@pytest.mark.parametrize("K,M,threads", [(20000, 1, 64), (3000, 4, 64), (3000, 16, 256), (2, 70, 5 * 256), (400, 70, 5 * 256)])
 def test_shift_scalars_take_no_more_threads_than_the_shifts_of_a_right_hand_side_need(K, M, threads, tmp_path):
     run(f"""
 _, H = upload(*band(64, 3))
