@@ -492,6 +492,51 @@ __global__ void __launch_bounds__(64) k_pupd(SolveDev s, int t)
     }
 }
 
+// k_pupd and k_rupd with one row per thread, for batches of uneven right-hand sides whose sums are not folded:
+// there the update and the seed iterations take about the same time, and workgroups of one wave with
+// four rows per lane take the places that the update's eight waves wait for (8 lattices of 16,000
+// to 250,000 rows, 32 right-hand sides each, FP32, 64 stored directions: 51.1 ms per update launch
+// against 48.5, 75.9 s per solve against 72.4).  Right-hand sides of one size gain 1 to 4 % from the
+// one-wave form, also beside the update.
+template <int RB>
+__global__ void __launch_bounds__(WG) k_pupd_rows(SolveDev s)
+{
+    const int2 it = s.it_grp[blockIdx.x];
+    if (it.x < 0) return;  // filler of an XCD set
+    const int64_t j0 = (int64_t)it.x * RB;
+    SeedState st[RB];
+    bool run[RB];
+    bool any = false;
+#pragma unroll
+    for (int b = 0; b < RB; ++b) {
+        run[b] = j0 + b < s.K;
+        if (run[b]) {
+            st[b] = s.seed[j0 + b];
+            run[b] = seed_running(st[b], s.TB);
+        }
+        any |= run[b];
+    }
+    if (!any) return;
+    const RhsDesc d = s.desc[j0];
+    const int64_t row = (int64_t)it.y * WG + threadIdx.x;
+    if (row >= d.n) return;
+    double2 *p = s.p + p_index(s, j0, d, row);
+    double2 pv[RB];
+#pragma unroll
+    for (int b = 0; b < RB; ++b) pv[b] = p[b];
+#pragma unroll
+    for (int b = 0; b < RB; ++b) {
+        if (run[b]) {
+            const double2 r = ring_slot(s, (st[b].base + st[b].step) % s.R, s.desc[j0 + b])[row];
+            pv[b] = cfma(st[b].beta_prev, pv[b], r);
+        }
+    }
+    // (stored after the loads of both)
+#pragma unroll
+    for (int b = 0; b < RB; ++b)
+        if (run[b]) p[b] = pv[b];
+}
+
 // Workgroups are dealt to the 8 XCDs round-robin by linear index.  With at least 8 groups of
 // right-hand sides every row block of one group is placed on the same XCD, so its vectors are
 // fetched into one L2 only: the 1-D grid has nblk * 8 * ceil(G / 8) workgroups and linear index
@@ -1011,6 +1056,36 @@ __global__ void __launch_bounds__(64) k_rupd(SolveDev s, int t)
         double2 *prr = FOLD ? ring_slot(s, (nslot + 1) % s.R, d) + rb : s.part2 + j * s.nblk + rb;
         *prr = rs;
         s.part1[j * s.nblk + rb] = ns;
+    }
+}
+
+__global__ void __launch_bounds__(WG) k_rupd_rows(SolveDev s)
+{
+    __shared__ double2 sh2[WG];
+    __shared__ double sh1[WG];
+    const int2 it = s.it_rhs[blockIdx.x];
+    const int64_t j = it.x, rb = it.y;
+    const SeedState st = s.seed[j];
+    if (!seed_running(st, s.TB)) return;
+    const RhsDesc d = s.desc[j];
+    const int64_t row = rb * WG + threadIdx.x;
+    const int slot = (st.base + st.step) % s.R;
+    const int nslot = (slot + 1) % s.R;
+    const double2 a = s.ahist[j * s.TB + st.step];
+    double2 rr = cmk(0, 0);
+    double nn = 0;
+    if (row < d.n) {
+        const double2 r = ring_slot(s, slot, d)[row];
+        const double2 q = s.q[d.voff + row];
+        const double2 rn = cfma(make_double2(-a.x, -a.y), q, r);
+        ring_slot(s, nslot, d)[row] = rn;
+        rr = csq_f(rn);
+        nn = cabs2_f(rn);
+    }
+    block_sum21(rr, nn, sh2, sh1);
+    if (threadIdx.x == 0) {
+        s.part2[j * s.nblk + rb] = rr;
+        s.part1[j * s.nblk + rb] = nn;
     }
 }
 
@@ -1898,9 +1973,13 @@ static hipError_t launch_seed_iteration(const SolveDev &s, int t, bool fold, hip
     const int64_t G = (s.K + RB - 1) / RB;
     const dim3 gp = s.it_grp ? dim3((unsigned)s.n_it_grp) : grid2(s.nblk, G);
     const bool folded = fold && t > 0;  // (the block's first iteration begins with a state that is up to date)
+    const bool rows = s.it_grp && !fold && !s.wproj;
     if (folded) {
         if (RB == 2) hipLaunchKernelGGL((k_pupd<2, true>), gp, dim3(64), 0, st, s, t);
         else hipLaunchKernelGGL((k_pupd<1, true>), gp, dim3(64), 0, st, s, t);
+    } else if (rows) {
+        if (RB == 2) hipLaunchKernelGGL(k_pupd_rows<2>, gp, dim3(WG), 0, st, s);
+        else hipLaunchKernelGGL(k_pupd_rows<1>, gp, dim3(WG), 0, st, s);
     } else {
         if (RB == 2) hipLaunchKernelGGL((k_pupd<2, false>), gp, dim3(64), 0, st, s, t);
         else hipLaunchKernelGGL((k_pupd<1, false>), gp, dim3(64), 0, st, s, t);
@@ -1933,7 +2012,8 @@ static hipError_t launch_seed_iteration(const SolveDev &s, int t, bool fold, hip
     }
     if (s.has_red_small) hipLaunchKernelGGL(k_alpha<WG>, dim3((unsigned)s.K), dim3(WG), 0, st, s);
     if (s.has_red_big) hipLaunchKernelGGL(k_alpha<RWG_BIG>, dim3((unsigned)s.K), dim3(RWG_BIG), 0, st, s);
-    hipLaunchKernelGGL(k_rupd<false>, gr, dim3(64), 0, st, s, t);
+    if (rows) hipLaunchKernelGGL(k_rupd_rows, gr, dim3(WG), 0, st, s);
+    else hipLaunchKernelGGL(k_rupd<false>, gr, dim3(64), 0, st, s, t);
     if (s.has_red_small) hipLaunchKernelGGL(k_beta<WG>, dim3((unsigned)s.K), dim3(WG), 0, st, s);
     if (s.has_red_big) hipLaunchKernelGGL(k_beta<RWG_BIG>, dim3((unsigned)s.K), dim3(RWG_BIG), 0, st, s);
     return hipGetLastError();

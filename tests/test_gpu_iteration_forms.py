@@ -100,3 +100,17 @@ def test_residuals_of_folded_and_separate_sums(n, rhs, block):
     rep1 = S.greens_diag(H, z, idx, tol=1e-6, block=block)[1]
     rep2 = S.greens_diag_batched([H, big], z, [idx, [0]], tol=1e-6, block=block)[1]
     assert np.array_equal(rep1["res"], rep2[0]["res"])
+
+
+@pytest.mark.parametrize("rhs,block", [(1, 1), (3, 0), (4, 8)])
+@pytest.mark.parametrize("n", [65537, 66000])
+def test_one_row_per_thread_in_uneven_batches(n, rhs, block):
+    """Batches of uneven right-hand sides beyond the folded sums against the same right-hand sides alone."""
+    H, small = _band(n, 7), _band(4500, 7)
+    z = np.linspace(-1.5, 1.5, 6) + 0.3j
+    idx = [(k * 977 + 3) % n for k in range(rhs)]
+    G1, rep1 = S.greens_diag(H, z, idx, tol=1e-6, block=block)[:2]
+    G2, rep2 = S.greens_diag_batched([small, H], z, [[0], idx], tol=1e-6, block=block)[:2]
+    assert torch.equal(G1, G2[1])
+    for key in ("iters", "status", "res"):
+        assert np.array_equal(rep1[key], rep2[1][key])

@@ -135,3 +135,13 @@ for n, K, folded in ((5000, 3, True), (5000, 1, True), (66000, 3, False), (66000
     assert plain > 0 and state == (3 * plain if folded else 0), (n, K, plain, state)
     lib.csr_free(H)
 """, tmp_path)
+
+
+def test_uneven_batches_beyond_the_folded_sums_keep_one_row_per_thread(tmp_path):
+    run(_SEED_BLOCK + """
+for matrices, rows in (((band(66000, 3), band(300, 3)), True), ((band(6000, 3), band(300, 3)), False),
+                       ((band(66000, 3), band(66000, 3)), False)):
+    one_launch(2, *matrices)
+    assert (launched('k_pupd_rows') > 0) == rows and (launched('k_rupd_rows') > 0) == rows
+    assert (launched('k_pupdI') > 0) != rows and (launched('k_rupdI') > 0) != rows
+""", tmp_path)
