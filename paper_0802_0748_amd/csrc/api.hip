@@ -1124,22 +1124,25 @@ int solve(SolveRequest &rq, hipStream_t st)
         sp[q].nact = s.nact + q * KM;
         sp[q].blk = s.blk + q * (size_t)K * 4;
     }
-    // update-kernel timing: a ring of event pairs on the update stream, read back lazily
+    // update-kernel timing: a ring of event pairs on the update stream, read back lazily, per block
+    // (those launched past the last one that did anything are left out at the end)
     constexpr int NE = 8;
     hipEvent_t fev[2 * NE] = {};
-    bool fev_pending[NE] = {};
+    int64_t fev_block[NE];
+    std::fill(fev_block, fev_block + NE, -1);
+    std::vector<float> update_ms;
     if (g_profiling)
         for (int q = 0; q < 2 * NE; ++q) HIPCHK(new_event(fev[q], hipEventDefault));
     auto collect = [&](int slot) -> hipError_t {
-        if (!fev_pending[slot]) return hipSuccess;
+        if (fev_block[slot] < 0) return hipSuccess;
         hipError_t r = hipEventSynchronize(fev[2 * slot + 1]);
         if (r != hipSuccess) return r;
         float ms = 0;
         r = hipEventElapsedTime(&ms, fev[2 * slot], fev[2 * slot + 1]);
         if (r != hipSuccess) return r;
-        g_timing.update_ms += ms;
-        g_timing.update_launches += 1;
-        fev_pending[slot] = false;
+        if ((int64_t)update_ms.size() <= fev_block[slot]) update_ms.resize(fev_block[slot] + 1);
+        update_ms[fev_block[slot]] = ms;
+        fev_block[slot] = -1;
         return hipSuccess;
     };
 
@@ -1175,8 +1178,7 @@ int solve(SolveRequest &rq, hipStream_t st)
     bool done = false;
     // A block of five launches is too short to wait for the host's look at the states after each:
     // the next round is launched first (a round too many costs its empty launches, about 15 us).
-    // Not while the update's launches are timed: the empty ones would count among them.
-    const bool ahead = s.seed_block != 0 && !g_profiling;
+    const bool ahead = s.seed_block != 0;
     int64_t rounds = 0;
     hipEvent_t evST[2] = {};
     if (ahead)
@@ -1204,7 +1206,7 @@ int solve(SolveRequest &rq, hipStream_t st)
             HIPCHK(launch_flush(sp[par], sf));
             if (g_profiling) {
                 HIPCHK(hipEventRecord(fev[2 * slot + 1], sf));
-                fev_pending[slot] = true;
+                fev_block[slot] = blocks;
             }
             if (overlap) HIPCHK(hipEventRecord(evFL[par], sf));
             if (use_graph) HIPCHK(hipGraphLaunch(gr.eb, st));
@@ -1237,6 +1239,10 @@ int solve(SolveRequest &rq, hipStream_t st)
     HIPCHK(hipStreamSynchronize(sf));
     if (g_profiling)
         for (int q = 0; q < NE; ++q) HIPCHK(collect(q));
+    for (int64_t b = 0; b < std::min<int64_t>(blocks, (int64_t)update_ms.size()); ++b) {
+        g_timing.update_ms += update_ms[b];
+        g_timing.update_launches += 1;
+    }
     int64_t iters_total = 0, switches = 0;
     for (int64_t j = 0; j < K; ++j) {
         iters_total += hs[j].iter;
